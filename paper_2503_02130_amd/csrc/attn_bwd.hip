@@ -952,158 +952,6 @@ __global__ __launch_bounds__(kDsThreads) void bwd_dq_stored_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// fp32 kernels: G = D/32 lanes per row, each lane owning 32 head dims.
-// ---------------------------------------------------------------------------
-constexpr int kF32Threads = 256;
-constexpr int kF32Tile = 32;
-
-template <int D, bool FIXED>
-__global__ __launch_bounds__(kF32Threads) void bwd_dq_f32_kernel(
-    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
-    const float* __restrict__ gate, const float* __restrict__ LSE, const float* __restrict__ dO,
-    const float* __restrict__ delta, float* __restrict__ dQ, float* __restrict__ dcq, int H,
-    int L, int n_blk, float scale, float scale_log2) {
-  constexpr int G = D / 32;
-  constexpr int RPW = kF32Threads / G;
-  __shared__ float ks[kF32Tile][D + 1];
-  __shared__ float vs[kF32Tile][D + 1];
-  __shared__ float cks[kF32Tile];
-  const int tid = threadIdx.x, sub = tid % G;
-  const int bh = (int)(blockIdx.x / n_blk);
-  const size_t head = (size_t)bh * (size_t)L;
-  const int q0 = (int)(blockIdx.x % n_blk) * RPW;
-  const int qi = q0 + tid / G;
-  const bool q_valid = qi < L;
-  const GateRow<FIXED> gr(gate, bh, H, head);
-  float qv[32], gv[32], acc[32];
-#pragma unroll
-  for (int e = 0; e < 32; ++e) {
-    qv[e] = q_valid ? Q[(head + qi) * D + sub * 32 + e] : 0.0f;
-    gv[e] = q_valid ? dO[(head + qi) * D + sub * 32 + e] : 0.0f;
-    acc[e] = 0.0f;
-  }
-  const float cq = q_valid ? gr.diff(qi, q0) : 0.0f;
-  const float lq = q_valid ? LSE[head + qi] : INFINITY;
-  const float dlt = q_valid ? delta[head + qi] : 0.0f;
-  float dc = 0.0f;
-  const int kend = min(L, q0 + RPW);
-  for (int key0 = 0; key0 < kend; key0 += kF32Tile) {
-    __syncthreads();
-    for (int i = tid; i < kF32Tile * D; i += kF32Threads) {
-      const int r = i / D, e = i % D, key = key0 + r;
-      ks[r][e] = key < L ? K[(head + key) * D + e] : 0.0f;
-      vs[r][e] = key < L ? V[(head + key) * D + e] : 0.0f;
-    }
-    if (tid < kF32Tile) {
-      const int key = key0 + tid;
-      cks[tid] = key < L ? gr.diff(key, q0) : INFINITY;
-    }
-    __syncthreads();
-    for (int j = 0; j < kF32Tile; ++j) {
-      float s = 0.0f, dp = 0.0f;
-#pragma unroll
-      for (int e = 0; e < 32; ++e) {
-        s += qv[e] * ks[j][sub * 32 + e];
-        dp += gv[e] * vs[j][sub * 32 + e];
-      }
-#pragma unroll
-      for (int off = 1; off < G; off <<= 1) {
-        s += __shfl_xor(s, off);
-        dp += __shfl_xor(dp, off);
-      }
-      float p = exp2_fast(s * scale_log2 + ((cq - cks[j]) - lq) * kLog2e);
-      if (key0 + j > qi) p = 0.0f;
-      const float ds = p * (dp - dlt);
-      dc += ds;
-#pragma unroll
-      for (int e = 0; e < 32; ++e) acc[e] += ds * ks[j][sub * 32 + e];
-    }
-  }
-  if (q_valid) {
-#pragma unroll
-    for (int e = 0; e < 32; ++e) dQ[(head + qi) * D + sub * 32 + e] = acc[e] * scale;
-    if (sub == 0) dcq[head + qi] = dc;
-  }
-}
-
-template <int D, bool FIXED>
-__global__ __launch_bounds__(kF32Threads) void bwd_dkdv_f32_kernel(
-    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
-    const float* __restrict__ gate, const float* __restrict__ LSE, const float* __restrict__ dO,
-    const float* __restrict__ delta, float* __restrict__ dK, float* __restrict__ dV,
-    float* __restrict__ dck, int H, int L, int n_blk, float scale, float scale_log2) {
-  constexpr int G = D / 32;
-  constexpr int RPW = kF32Threads / G;
-  __shared__ float qs[kF32Tile][D + 1];
-  __shared__ float gs[kF32Tile][D + 1];
-  __shared__ float cqs[kF32Tile];
-  __shared__ float lqs[kF32Tile];
-  __shared__ float dls[kF32Tile];
-  const int tid = threadIdx.x, sub = tid % G;
-  const int bh = (int)(blockIdx.x / n_blk);
-  const size_t head = (size_t)bh * (size_t)L;
-  const int k0 = (int)(blockIdx.x % n_blk) * RPW;
-  const int kj = k0 + tid / G;
-  const bool k_valid = kj < L;
-  const GateRow<FIXED> gr(gate, bh, H, head);
-  float kv[32], vv[32], ak[32], av[32];
-#pragma unroll
-  for (int e = 0; e < 32; ++e) {
-    kv[e] = k_valid ? K[(head + kj) * D + sub * 32 + e] : 0.0f;
-    vv[e] = k_valid ? V[(head + kj) * D + sub * 32 + e] : 0.0f;
-    ak[e] = 0.0f;
-    av[e] = 0.0f;
-  }
-  const float ck = k_valid ? gr.diff(kj, k0) : -INFINITY;
-  float dc = 0.0f;
-  for (int qs0 = k0; qs0 < L; qs0 += kF32Tile) {
-    __syncthreads();
-    for (int i = tid; i < kF32Tile * D; i += kF32Threads) {
-      const int r = i / D, e = i % D, qq = qs0 + r;
-      qs[r][e] = qq < L ? Q[(head + qq) * D + e] : 0.0f;
-      gs[r][e] = qq < L ? dO[(head + qq) * D + e] : 0.0f;
-    }
-    if (tid < kF32Tile) {
-      const int qq = qs0 + tid;
-      cqs[tid] = qq < L ? gr.diff(qq, k0) : 0.0f;
-      lqs[tid] = qq < L ? LSE[head + qq] : INFINITY;
-      dls[tid] = qq < L ? delta[head + qq] : 0.0f;
-    }
-    __syncthreads();
-    for (int i = 0; i < kF32Tile; ++i) {
-      float s = 0.0f, dp = 0.0f;
-#pragma unroll
-      for (int e = 0; e < 32; ++e) {
-        s += kv[e] * qs[i][sub * 32 + e];
-        dp += vv[e] * gs[i][sub * 32 + e];
-      }
-#pragma unroll
-      for (int off = 1; off < G; off <<= 1) {
-        s += __shfl_xor(s, off);
-        dp += __shfl_xor(dp, off);
-      }
-      float p = exp2_fast(s * scale_log2 + ((cqs[i] - ck) - lqs[i]) * kLog2e);
-      if (kj > qs0 + i || !k_valid) p = 0.0f;
-      const float ds = p * (dp - dls[i]);
-      dc -= ds;
-#pragma unroll
-      for (int e = 0; e < 32; ++e) {
-        av[e] += p * gs[i][sub * 32 + e];
-        ak[e] += ds * qs[i][sub * 32 + e];
-      }
-    }
-  }
-  if (k_valid) {
-#pragma unroll
-    for (int e = 0; e < 32; ++e) {
-      dK[(head + kj) * D + sub * 32 + e] = ak[e] * scale;
-      dV[(head + kj) * D + sub * 32 + e] = av[e];
-    }
-    if (sub == 0) dck[head + kj] = dc;
-  }
-}
-
-// ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
 template <typename T>
@@ -1128,92 +976,71 @@ hipError_t launch_bwd_delta(bool bf16_, const void* o, const void* d_o, float* d
 }
 
 template <int D, bool FIXED>
-static void dkdv_t(bool bf16_, const void* q, const void* k, const void* v, GateSpec g,
-                   const float* lse, const void* d_o, const float* delta, void* dk, void* dv,
-                   float* dck, int BH, int L, float scale, hipStream_t s, const float* qn,
-                   const float* kn) {
+static void dkdv_t(const void* q, const void* k, const void* v, GateSpec g, const float* lse,
+                   const void* d_o, const float* delta, void* dk, void* dv, float* dck, int BH,
+                   int L, float scale, hipStream_t s, const float* qn, const float* kn) {
   const float sl2 = scale * kLog2e;
-  if (bf16_) {
-    const dim3 grid((unsigned)((L + kKvBN - 1) / kKvBN) * (unsigned)BH);
-    if (qn)
-      hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<D, FIXED, true>), grid, dim3(kKvThreads), 0, s,
-                         (const bf16*)q, (const bf16*)k, (const bf16*)v, g.ptr, qn, kn, lse,
-                         (const bf16*)d_o, delta, (bf16*)dk, (bf16*)dv, dck, nullptr, nullptr, BH, g.H, L, scale,
-                         sl2);
-    else
+  const dim3 grid((unsigned)((L + kKvBN - 1) / kKvBN) * (unsigned)BH);
+  if (qn)
+    hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<D, FIXED, true>), grid, dim3(kKvThreads), 0, s,
+                       (const bf16*)q, (const bf16*)k, (const bf16*)v, g.ptr, qn, kn, lse,
+                       (const bf16*)d_o, delta, (bf16*)dk, (bf16*)dv, dck, nullptr, nullptr, BH,
+                       g.H, L, scale, sl2);
+  else
     hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<D, FIXED, false>), grid, dim3(kKvThreads), 0, s,
                        (const bf16*)q, (const bf16*)k, (const bf16*)v, g.ptr, qn, kn, lse,
-                       (const bf16*)d_o, delta, (bf16*)dk, (bf16*)dv, dck, nullptr, nullptr, BH, g.H, L, scale,
-                       sl2);
-  } else {
-    const int rpw = kF32Threads / (D / 32);
-    const int n_blk = (L + rpw - 1) / rpw;
-    const dim3 grid((unsigned)n_blk * (unsigned)BH);
-    hipLaunchKernelGGL((bwd_dkdv_f32_kernel<D, FIXED>), grid, dim3(kF32Threads), 0, s,
-                       (const float*)q, (const float*)k, (const float*)v, g.ptr, lse,
-                       (const float*)d_o, delta, (float*)dk, (float*)dv, dck, g.H, L, n_blk,
-                       scale, sl2);
-  }
+                       (const bf16*)d_o, delta, (bf16*)dk, (bf16*)dv, dck, nullptr, nullptr, BH,
+                       g.H, L, scale, sl2);
 }
 
 hipError_t launch_bwd_dkdv(bool bf16_, const void* q, const void* k, const void* v, GateSpec g,
                            const float* lse, const void* d_o, const float* delta, void* dk,
                            void* dv, float* dck, int BH, int L, int d, float scale,
                            hipStream_t s, const float* qn, const float* kn) {
+  if (!bf16_)
+    return launch_bwd_dkdv_f32((const float*)q, (const float*)k, (const float*)v, g, lse,
+                               (const float*)d_o, delta, (float*)dk, (float*)dv, dck, BH, L, d,
+                               scale, s);
   if (d == 128) {
-    if (g.fixed)
-      dkdv_t<128, true>(bf16_, q, k, v, g, lse, d_o, delta, dk, dv, dck, BH, L, scale, s, qn, kn);
-    else
-      dkdv_t<128, false>(bf16_, q, k, v, g, lse, d_o, delta, dk, dv, dck, BH, L, scale, s, qn, kn);
+    if (g.fixed) dkdv_t<128, true>(q, k, v, g, lse, d_o, delta, dk, dv, dck, BH, L, scale, s, qn, kn);
+    else dkdv_t<128, false>(q, k, v, g, lse, d_o, delta, dk, dv, dck, BH, L, scale, s, qn, kn);
   } else {
-    if (g.fixed)
-      dkdv_t<64, true>(bf16_, q, k, v, g, lse, d_o, delta, dk, dv, dck, BH, L, scale, s, qn, kn);
-    else
-      dkdv_t<64, false>(bf16_, q, k, v, g, lse, d_o, delta, dk, dv, dck, BH, L, scale, s, qn, kn);
+    if (g.fixed) dkdv_t<64, true>(q, k, v, g, lse, d_o, delta, dk, dv, dck, BH, L, scale, s, qn, kn);
+    else dkdv_t<64, false>(q, k, v, g, lse, d_o, delta, dk, dv, dck, BH, L, scale, s, qn, kn);
   }
   return hipGetLastError();
 }
 
 template <int D, bool FIXED>
-static void dq_t(bool bf16_, const void* q, const void* k, const void* v, GateSpec g,
-                 const float* lse, const void* d_o, const float* delta, void* dq, float* dcq,
-                 int BH, int L, float scale, hipStream_t s, const float* qn, const float* kn) {
+static void dq_t(const void* q, const void* k, const void* v, GateSpec g, const float* lse,
+                 const void* d_o, const float* delta, void* dq, float* dcq, int BH, int L,
+                 float scale, hipStream_t s, const float* qn, const float* kn) {
   const float sl2 = scale * kLog2e;
-  if (bf16_) {
-    const int n_mblk = (L + kDqBM - 1) / kDqBM;
-    const dim3 grid((unsigned)n_mblk * (unsigned)BH);
-    if (qn)
-      hipLaunchKernelGGL((bwd_dq_bf16_kernel<D, FIXED, true>), grid, dim3(kBwdThreads), 0, s,
-                         (const bf16*)q, (const bf16*)k, (const bf16*)v, g.ptr, qn, kn, lse,
-                         (const bf16*)d_o, delta, (bf16*)dq, dcq, BH, g.H, L, n_mblk, scale, sl2);
-    else
+  const int n_mblk = (L + kDqBM - 1) / kDqBM;
+  const dim3 grid((unsigned)n_mblk * (unsigned)BH);
+  if (qn)
+    hipLaunchKernelGGL((bwd_dq_bf16_kernel<D, FIXED, true>), grid, dim3(kBwdThreads), 0, s,
+                       (const bf16*)q, (const bf16*)k, (const bf16*)v, g.ptr, qn, kn, lse,
+                       (const bf16*)d_o, delta, (bf16*)dq, dcq, BH, g.H, L, n_mblk, scale, sl2);
+  else
     hipLaunchKernelGGL((bwd_dq_bf16_kernel<D, FIXED, false>), grid, dim3(kBwdThreads), 0, s,
                        (const bf16*)q, (const bf16*)k, (const bf16*)v, g.ptr, qn, kn, lse,
                        (const bf16*)d_o, delta, (bf16*)dq, dcq, BH, g.H, L, n_mblk, scale, sl2);
-  } else {
-    const int rpw = kF32Threads / (D / 32);
-    const int n_blk = (L + rpw - 1) / rpw;
-    const dim3 grid((unsigned)n_blk * (unsigned)BH);
-    hipLaunchKernelGGL((bwd_dq_f32_kernel<D, FIXED>), grid, dim3(kF32Threads), 0, s,
-                       (const float*)q, (const float*)k, (const float*)v, g.ptr, lse,
-                       (const float*)d_o, delta, (float*)dq, dcq, g.H, L, n_blk, scale, sl2);
-  }
 }
 
 hipError_t launch_bwd_dq(bool bf16_, const void* q, const void* k, const void* v, GateSpec g,
                          const float* lse, const void* d_o, const float* delta, void* dq,
                          float* dcq, int BH, int L, int d, float scale, hipStream_t s,
                          const float* qn, const float* kn) {
+  if (!bf16_)
+    return launch_bwd_dq_f32((const float*)q, (const float*)k, (const float*)v, g, lse,
+                             (const float*)d_o, delta, (float*)dq, dcq, BH, L, d, scale, s);
   if (d == 128) {
-    if (g.fixed)
-      dq_t<128, true>(bf16_, q, k, v, g, lse, d_o, delta, dq, dcq, BH, L, scale, s, qn, kn);
-    else
-      dq_t<128, false>(bf16_, q, k, v, g, lse, d_o, delta, dq, dcq, BH, L, scale, s, qn, kn);
+    if (g.fixed) dq_t<128, true>(q, k, v, g, lse, d_o, delta, dq, dcq, BH, L, scale, s, qn, kn);
+    else dq_t<128, false>(q, k, v, g, lse, d_o, delta, dq, dcq, BH, L, scale, s, qn, kn);
   } else {
-    if (g.fixed)
-      dq_t<64, true>(bf16_, q, k, v, g, lse, d_o, delta, dq, dcq, BH, L, scale, s, qn, kn);
-    else
-      dq_t<64, false>(bf16_, q, k, v, g, lse, d_o, delta, dq, dcq, BH, L, scale, s, qn, kn);
+    if (g.fixed) dq_t<64, true>(q, k, v, g, lse, d_o, delta, dq, dcq, BH, L, scale, s, qn, kn);
+    else dq_t<64, false>(q, k, v, g, lse, d_o, delta, dq, dcq, BH, L, scale, s, qn, kn);
   }
   return hipGetLastError();
 }

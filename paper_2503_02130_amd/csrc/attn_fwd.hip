@@ -37,12 +37,6 @@
 //     tile holding its diagonal applies the mask.  Query blocks are dispatched
 //     longest-first with heads fastest, so a head's blocks share an XCD's L2
 //     whenever the head count is a multiple of 8.
-//
-// fp32 kernel: a straightforward vector-ALU kernel (D/32 lanes per query row,
-// keys staged through LDS 32 at a time).  It favours accuracy over speed: the
-// bias c_i - c_j is formed in natural-log units before the change to base 2, so
-// the row maximum stays small and the logsumexp carries no cancellation even
-// when c changes by thousands within a block.
 #include <type_traits>
 
 #include "fox_device.h"
@@ -429,88 +423,6 @@ void fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
   }
 }
 
-// ---------------------------------------------------------------------------
-// fp32 forward: G = D/32 lanes per query row, each lane owning 32 head dims.
-// ---------------------------------------------------------------------------
-constexpr int kF32Threads = 256;
-constexpr int kF32BN = 32;
-
-template <int D, bool FIXED>
-__global__ __launch_bounds__(kF32Threads) void fwd_f32_kernel(
-    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
-    const float* __restrict__ gate, float* __restrict__ O, float* __restrict__ LSE, int H, int L,
-    int n_blk, float scale_log2) {
-  constexpr int G = D / 32;
-  constexpr int RPW = kF32Threads / G;  // query rows per workgroup
-  __shared__ float ks[kF32BN][D + 1];
-  __shared__ float vs[kF32BN][D + 1];
-  __shared__ float cks[kF32BN];
-  const int tid = threadIdx.x;
-  const int sub = tid % G;
-  const int bh = (int)(blockIdx.x / n_blk);
-  const size_t head = (size_t)bh * (size_t)L;
-  const int q0 = (int)(blockIdx.x % n_blk) * RPW;
-  const int qi = q0 + tid / G;
-  const bool q_valid = qi < L;
-  const GateRow<FIXED> gr(gate, bh, H, head);
-  const float cq = q_valid ? gr.diff(qi, q0) : 0.0f;
-  float qv[32], ov[32];
-#pragma unroll
-  for (int e = 0; e < 32; ++e) {
-    qv[e] = q_valid ? Q[(head + qi) * D + sub * 32 + e] : 0.0f;
-    ov[e] = 0.0f;
-  }
-  float m_run = -INFINITY, l_run = 0.0f;
-  const int kend = min(L, q0 + RPW);
-  for (int key0 = 0; key0 < kend; key0 += kF32BN) {
-    __syncthreads();
-    for (int i = tid; i < kF32BN * D; i += kF32Threads) {
-      const int r = i / D, e = i % D, key = key0 + r;
-      ks[r][e] = key < L ? K[(head + key) * D + e] : 0.0f;
-      vs[r][e] = key < L ? V[(head + key) * D + e] : 0.0f;
-    }
-    if (tid < kF32BN) {
-      const int key = key0 + tid;
-      cks[tid] = key < L ? gr.diff(key, q0) : INFINITY;
-    }
-    __syncthreads();
-    float sc[kF32BN];
-    float mt = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < kF32BN; ++j) {
-      float part = 0.0f;
-#pragma unroll
-      for (int e = 0; e < 32; ++e) part += qv[e] * ks[j][sub * 32 + e];
-#pragma unroll
-      for (int off = 1; off < G; off <<= 1) part += __shfl_xor(part, off);
-      float x = part * scale_log2 + (cq - cks[j]) * kLog2e;
-      if (key0 + j > qi) x = -INFINITY;
-      sc[j] = x;
-      mt = fmaxf(mt, x);
-    }
-    // Key 0 lies in the first tile and is never masked, so m_new is finite.
-    const float m_new = fmaxf(m_run, mt);
-    const float alpha = exp2_fast(m_run - m_new);
-    l_run *= alpha;
-#pragma unroll
-    for (int e = 0; e < 32; ++e) ov[e] *= alpha;
-#pragma unroll
-    for (int j = 0; j < kF32BN; ++j) {
-      const float p = exp2_fast(sc[j] - m_new);
-      l_run += p;
-#pragma unroll
-      for (int e = 0; e < 32; ++e) ov[e] += p * vs[j][sub * 32 + e];
-    }
-    m_run = m_new;
-  }
-  if (q_valid) {
-    const float inv = 1.0f / l_run;
-#pragma unroll
-    for (int e = 0; e < 32; ++e) O[(head + qi) * D + sub * 32 + e] = ov[e] * inv;
-    if (sub == 0) LSE[head + qi] = kLn2 * (m_run + log2f(l_run));
-  }
-}
-
 template <int D, bool FIXED, bool SKIP>
 static void fwd_bf16_t(const void* q, const void* k, const void* v, GateSpec g,
                        const float* qn, const float* kn, void* o, float* lse, int BH, int L,
@@ -563,29 +475,6 @@ hipError_t launch_fwd_bf16_out_gate(const void* q, const void* k, const void* v,
   const OutGateArgs og{static_cast<const bf16*>(g), wo, eps, static_cast<bf16*>(y), H};
   if (d == 128) fwd_bf16_outg_t<128>(q, k, v, c, o, lse, og, BH, L, scale * kLog2e, s);
   else fwd_bf16_outg_t<64>(q, k, v, c, o, lse, og, BH, L, scale * kLog2e, s);
-  return hipGetLastError();
-}
-
-template <int D, bool FIXED>
-static void fwd_f32_t(const float* q, const float* k, const float* v, GateSpec g, float* o,
-                      float* lse, int BH, int L, float sl2, hipStream_t s) {
-  const int rpw = kF32Threads / (D / 32);
-  const int n_blk = (L + rpw - 1) / rpw;
-  const dim3 grid((unsigned)n_blk * (unsigned)BH);
-  hipLaunchKernelGGL((fwd_f32_kernel<D, FIXED>), grid, dim3(kF32Threads), 0, s, q, k, v, g.ptr,
-                     o, lse, g.H, L, n_blk, sl2);
-}
-
-hipError_t launch_fwd_f32(const float* q, const float* k, const float* v, GateSpec g, float* o,
-                          float* lse, int BH, int L, int d, float scale, hipStream_t s) {
-  const float sl2 = scale * kLog2e;
-  if (d == 128) {
-    if (g.fixed) fwd_f32_t<128, true>(q, k, v, g, o, lse, BH, L, sl2, s);
-    else fwd_f32_t<128, false>(q, k, v, g, o, lse, BH, L, sl2, s);
-  } else {
-    if (g.fixed) fwd_f32_t<64, true>(q, k, v, g, o, lse, BH, L, sl2, s);
-    else fwd_f32_t<64, false>(q, k, v, g, o, lse, BH, L, sl2, s);
-  }
   return hipGetLastError();
 }
 

@@ -48,6 +48,14 @@ hipError_t launch_bwd_dq(bool bf16, const void* q, const void* k, const void* v,
                          const float* lse, const void* d_o, const float* delta, void* dq,
                          float* dcq, int BH, int L, int d, float scale, hipStream_t s,
                          const float* q_norm_max = nullptr, const float* k_norm_max = nullptr);
+// the fp32 halves of the two above (attn_f32.hip; dense, whatever the gates)
+hipError_t launch_bwd_dkdv_f32(const float* q, const float* k, const float* v, GateSpec g,
+                               const float* lse, const float* d_o, const float* delta, float* dk,
+                               float* dv, float* dck, int BH, int L, int d, float scale,
+                               hipStream_t s);
+hipError_t launch_bwd_dq_f32(const float* q, const float* k, const float* v, GateSpec g,
+                             const float* lse, const float* d_o, const float* delta, float* dq,
+                             float* dcq, int BH, int L, int d, float scale, hipStream_t s);
 hipError_t launch_bwd(bool bf16, const void* q, const void* k, const void* v, const float* c,
                       const void* o, const float* lse, const void* d_o, void* dq, void* dk,
                       void* dv, float* d_log_f, void* ws, int BH, int L, int d, float scale,
