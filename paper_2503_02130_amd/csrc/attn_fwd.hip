@@ -33,6 +33,12 @@
 //     rescaled.  Exponents up to 8 are absorbed by bf16 P and the fp32 sums.
 //   * l sums P after its rounding to bf16 (v_dot2_f32_bf16 against ones), the
 //     same values the P V product uses.
+//   * Where the grid leaves CUs or SIMDs idle, the workgroup gets KS = 2 or 4 groups of
+//     four waves (fwd_groups): group g visits tiles t_last - g, - KS, .., with its own
+//     tile buffers and its own barrier (a count in LDS: with the workgroup's barrier
+//     the groups run in phase and do not fill each other's gaps, at D = 64 10-20 %
+//     slower), and the groups' O, l and m merge in LDS at the end.  B H = 16,
+//     L = 3001: 67.8 -> 55.7 us at D = 128, 46.3 -> 37.0 us at D = 64.
 //   * Causal structure: tiles after a wave's last query are skipped and only the
 //     tile holding its diagonal applies the mask.  Query blocks are dispatched
 //     longest-first with heads fastest, so a head's blocks share an XCD's L2
@@ -61,6 +67,26 @@ struct FwdSmem {
   bf16 v[2][kFwdBN * D];
   float c[2][kFwdBN];
 };
+// With the keys split over wave groups, a group's tiles also hold its O partial, and
+// its running maxima and sums follow them.  The alignment keeps the next group's tiles
+// on 16-byte boundaries.
+template <int D, int KS>
+struct alignas(256) FwdGroupSmem : FwdSmem<D> {
+  float stat[kFwdWaves][2][64];  // m and l of each lane
+  uint32_t arrived;              // waves of the group that reached its next tile, running
+};
+template <int D>
+struct FwdGroupSmem<D, 1> : FwdSmem<D> {};
+
+// Barrier of one wave group: each wave adds itself to the group's count and waits
+// until the count says that all of them arrived.  The waves of a workgroup are
+// resident together and each arrives once per target, so every wait ends.
+__device__ __forceinline__ void group_sync(uint32_t* arrived, uint32_t target) {
+  if ((threadIdx.x & 63) == 0)
+    __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+  while (__hip_atomic_load(arrived, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < target) {
+  }
+}
 
 // SKIP: qnorm, knorm [BH] bound the row norms of Q and K.  For a query block
 // starting at q0 and a key tile ending at jl, every score is at most
@@ -78,8 +104,8 @@ struct FwdSmem {
 // Occupancy: two waves per SIMD at D = 128 (about 240 VGPRs); at D = 64 the
 // kernel fits 128 VGPRs and runs four (the LDS would allow four workgroups per
 // CU; measured 3 % faster than three).
-template <int D, bool FIXED, bool SKIP, bool OUTG = false>
-__global__ __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
+template <int D, bool FIXED, bool SKIP, bool OUTG, int KS>
+__global__ __launch_bounds__(kFwdThreads * KS) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
 void fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
                      const bf16* __restrict__ V, const float* __restrict__ gate,
                      const float* __restrict__ qnorm, const float* __restrict__ knorm,
@@ -87,9 +113,11 @@ void fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
                      int n_mblk, float scale_log2, OutGateArgs og) {
   constexpr int TILE = kFwdBN * D;                         // bf16 elements per tile
   constexpr int NDMA = TILE * 2 / 1024 / kFwdWaves;        // 1 KB DMA loads per wave per tile
-  __shared__ __attribute__((aligned(16))) FwdSmem<D> sm;
+  __shared__ __attribute__((aligned(16))) FwdGroupSmem<D, KS> smem[KS];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = (tid >> 6) % kFwdWaves;
+  const int grp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / kFwdThreads);
+  FwdGroupSmem<D, KS>& sm = smem[grp];  // this group's tiles
   const int h = lane >> 5, col = lane & 31;
   // heads fastest (a head's blocks on one XCD, sharing its L2); with skipping the
   // work per head depends on its gates, so the heads rotate over the XCDs
@@ -169,6 +197,39 @@ void fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
       sm.c[B][lane] = ckey < L ? gr.diff_raw(q0, c_q0, ckey, craw) * inv_scale : -INFINITY;
   };
 
+  // a row's maximum over the 64 keys of a tile
+  auto max32 = [&](const float* u) {
+    float mt = u[0];
+#pragma unroll
+    for (int r = 1; r < 32; ++r) mt = fmaxf(mt, u[r]);
+    return wave_max_pair(mt);
+  };
+  // S^T of 32 keys from key0 on of a staged tile: the diagonal tile's order, masked
+  auto masked_scores = [&](const bf16* kt_, const float* ct_, int key0, float m_sub, float* u) {
+    bf16x8 ka[D / 16];
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) ka[s] = *reinterpret_cast<const bf16x8*>(kt_ + koff[s]);
+    f32x16 acc;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const f32x4 ck4 = *reinterpret_cast<const f32x4*>(ct_ + 8 * g + 4 * h);
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) acc[4 * g + jj] = ck4[jj];
+    }
+    sched_fence();
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) acc = mfma32(ka[s], qf[s], acc);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) {
+        float x = acc[4 * g + jj] * scale_log2 - m_sub;
+        if (key0 + 8 * g + 4 * h + jj > qi) x = -INFINITY;
+        u[4 * g + jj] = x;
+      }
+    }
+  };
+
   auto tile_body = [&](int j, auto bufc, auto masked) {
     constexpr int B = decltype(bufc)::value;
     constexpr bool MASK = decltype(masked)::value;
@@ -238,31 +299,8 @@ void fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
       }
     } else {  // the diagonal tile: plain order, then the causal mask
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        bf16x8 ka[D / 16];
-#pragma unroll
-        for (int s = 0; s < D / 16; ++s)
-          ka[s] = *reinterpret_cast<const bf16x8*>(kt_ + kb * 32 * D + koff[s]);
-        f32x16 acc;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x4 ck4 = *reinterpret_cast<const f32x4*>(ct_ + kb * 32 + 8 * g + 4 * h);
-#pragma unroll
-          for (int jj = 0; jj < 4; ++jj) acc[4 * g + jj] = ck4[jj];
-        }
-        sched_fence();
-#pragma unroll
-        for (int s = 0; s < D / 16; ++s) acc = mfma32(ka[s], qf[s], acc);
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-#pragma unroll
-          for (int jj = 0; jj < 4; ++jj) {
-            float x = acc[4 * g + jj] * scale_log2 - m_sub;
-            if (MASK && key0 + kb * 32 + 8 * g + 4 * h + jj > qi) x = -INFINITY;
-            u[kb * 16 + 4 * g + jj] = x;
-          }
-        }
-      }
+      for (int kb = 0; kb < 2; ++kb)
+        masked_scores(kt_ + kb * 32 * D, ct_ + kb * 32, key0 + kb * 32, m_sub, u + 16 * kb);
     }
     // rescale O and l by 2^-shift and take u relative to the new maximum
     auto rescale = [&](float shift) {
@@ -273,12 +311,7 @@ void fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
 #pragma unroll
       for (int r = 0; r < 32; ++r) u[r] -= shift;
     };
-    auto tile_max = [&]() {
-      float mt = u[0];
-#pragma unroll
-      for (int r = 1; r < 32; ++r) mt = fmaxf(mt, u[r]);
-      return wave_max_pair(mt);
-    };
+    auto tile_max = [&]() { return max32(u); };
     auto exponentiate = [&]() {
       float psum = 0.0f;
 #pragma unroll
@@ -340,32 +373,105 @@ void fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
     });
   };
 
+  // Group g visits tiles t_last - g, - KS, ...  Before tile j is read: its DMA has
+  // arrived and every wave of the group is done with the tile before it.
+  uint32_t arrivals = 0;
+  auto tile_ready = [&]() {
+    wait_all_memory();
+    if constexpr (KS == 1) {
+      __syncthreads();
+    } else {
+      group_sync(&smem[grp].arrived, arrivals += kFwdWaves);
+    }
+  };
   // returns true when tile j and all earlier tiles can be skipped
+  const int j0 = t_last - grp;
   auto step = [&](int j, auto bufc) {
     constexpr int B = decltype(bufc)::value;
-    wait_all_memory();
-    __syncthreads();  // tile j is in LDS; every wave is done with tile j + 1
+    if (KS == 1 || j != j0) tile_ready();  // split, the first tile is awaited below
     if constexpr (SKIP) {
       // the tile's last key is the least decayed one (full tiles only: the
       // diagonal region never passes the test)
       if (j < t_last && scale_log2 * (skip_norm + sm.c[B][kFwdBN - 1]) < -kSkipMargin)
         return true;
     }
-    if (j > 0) issue_tile(j - 1, std::integral_constant<int, 1 - B>());
+    if (j >= KS) issue_tile(j - KS, std::integral_constant<int, 1 - B>());
     if (j == t_diag) {
       tile_body(j, bufc, std::true_type());
     } else if (j < t_diag) {
       tile_body(j, bufc, std::false_type());
     }
-    if (j > 0) store_c(std::integral_constant<int, 1 - B>());
+    if (j >= KS) store_c(std::integral_constant<int, 1 - B>());
     return false;
   };
 
-  issue_tile(t_last, std::integral_constant<int, 0>());
-  store_c(std::integral_constant<int, 0>());
-  for (int j = t_last; j >= 0; j -= 2) {
+  if (KS == 1 || j0 >= 0) {
+    issue_tile(j0, std::integral_constant<int, 0>());
+    store_c(std::integral_constant<int, 0>());
+  }
+  if constexpr (KS > 1) {
+    if (tid < KS) smem[tid].arrived = 0;
+    wait_all_memory();
+    __syncthreads();  // every group's first tile is in LDS
+    // A wave whose diagonal tile is another group's takes its row maximum too: every
+    // group then works from the reference the unsplit kernel has, and a skipped tile
+    // is an exact zero in each of them.
+    if (j0 >= 0 && j0 != t_diag && t_diag <= t_last) {
+      const FwdSmem<D>& sd = smem[t_last - t_diag];
+      float u[32];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+        masked_scores(sd.k[0] + kb * 32 * D, sd.c[0] + kb * 32, t_diag * kFwdBN + kb * 32, 0.0f,
+                      u + 16 * kb);
+      m_used = max32(u);
+    }
+    __syncthreads();  // the groups go on by themselves
+  }
+  for (int j = j0; j >= 0; j -= 2 * KS) {
     if (step(j, std::integral_constant<int, 0>())) break;
-    if (j > 0 && step(j - 1, std::integral_constant<int, 1>())) break;
+    if (j >= KS && step(j - KS, std::integral_constant<int, 1>())) break;
+  }
+
+  if constexpr (KS > 1) {
+    // merge the groups: groups 1.. leave O, l and m of each lane in their tiles, the
+    // lanes of group 0 that hold the same elements add them up
+    __syncthreads();
+    f32x4* part = reinterpret_cast<f32x4*>(&sm.k[0][0]) + wave * (D / 8) * 64 + lane;
+    float* stat = &smem[grp].stat[wave][0][lane];
+    if (grp > 0) {
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          part[(4 * db + g) * 64] = f32x4{oacc[db][4 * g], oacc[db][4 * g + 1],
+                                          oacc[db][4 * g + 2], oacc[db][4 * g + 3]};
+      stat[0] = m_used;
+      stat[64] = l_run;
+    }
+    __syncthreads();
+    if (grp > 0) return;
+    float M = m_used;
+#pragma unroll
+    for (int k = 1; k < KS; ++k) M = fmaxf(M, smem[k].stat[wave][0][lane]);
+    const float f0 = exp2_fast(m_used - M);
+    m_used = M;
+    l_run *= f0;
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db) oacc[db] *= f0;
+#pragma unroll
+    for (int k = 1; k < KS; ++k) {
+      const float f = exp2_fast(smem[k].stat[wave][0][lane] - M);
+      l_run += f * smem[k].stat[wave][1][lane];
+      const f32x4* pk = reinterpret_cast<const f32x4*>(&smem[k].k[0][0]) + wave * (D / 8) * 64 + lane;
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x4 v = pk[(4 * db + g) * 64];
+#pragma unroll
+          for (int jj = 0; jj < 4; ++jj) oacc[db][4 * g + jj] += f * v[jj];
+        }
+    }
   }
 
   const float l_tot = wave_sum_pair(l_run);
@@ -423,15 +529,58 @@ void fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
   }
 }
 
-template <int D, bool FIXED, bool SKIP>
-static void fwd_bf16_t(const void* q, const void* k, const void* v, GateSpec g,
+// Wave groups of a workgroup (KS): 1 where the grid fills the part, more where it does
+// not and the longest row's chain of key tiles decides the time.  The split costs a
+// merge (and at D = 128 the second, independent workgroup of a CU), so short rows and
+// full grids keep the unsplit kernel.  Measured (graph replay, us; workgroups x key
+// tiles of the longest row: KS = 1 / 2 / 4):
+//   D = 64:  128 x 16: 17.5 / 16.5 / 16.6    256 x 32: 31.1 / 27.3 / 26.0
+//            384 x 47: 46.3 / 41.1 / 37.0    512 x 32: 36.8 / 35.0 / 36.9
+//            512 x 256: 226 / 193 / 169      640 x 79: 79.9 / 74.8 / 81.6
+//            1024 x 128: 167 / 160 / 176     960 x 19: 33.0 / 35.2 / 50.5
+//            384 x 5: 9.4 / 10.6 / 16.2      4096 x 256: 1054 / 1107 / 1223
+//   D = 128: 256 x 16: 25.5 / 24.7           256 x 32: 43.8 / 38.6
+//            384 x 47: 67.8 / 55.7           512 x 32: 56.3 / 55.2
+//            512 x 256: 354 / 271            512 x 16: 32.8 / 37.7
+//            640 x 79: 121 / 130             576 x 47: 74.7 / 81.5
+//            1024 x 128: 277 / 287           4096 x 256: 1917 / 2066
+// The rule takes shapes only, so that skipping and dense calls split alike.
+template <int D>
+static int fwd_groups(int BH, int L) {
+  const long long wgs = (long long)BH * ((L + kFwdBM - 1) / kFwdBM);
+  const long long tiles = (L + kFwdBN - 1) / kFwdBN;
+  if (D == 64) {
+    if (wgs <= 512 && tiles >= 24 && 12 * tiles >= wgs) return 4;
+    return wgs <= 1024 && tiles >= 12 && 16 * tiles >= wgs ? 2 : 1;
+  }
+  return wgs <= 512 && tiles >= 16 && 16 * tiles >= wgs ? 2 : 1;
+}
+
+template <int D, bool FIXED, bool SKIP, int KS>
+static void fwd_bf16_k(const void* q, const void* k, const void* v, GateSpec g,
                        const float* qn, const float* kn, void* o, float* lse, int BH, int L,
                        float sl2, hipStream_t s) {
   const int n_mblk = (L + kFwdBM - 1) / kFwdBM;
   const dim3 grid((unsigned)n_mblk * (unsigned)BH);
-  hipLaunchKernelGGL((fwd_bf16_kernel<D, FIXED, SKIP>), grid, dim3(kFwdThreads), 0, s,
+  hipLaunchKernelGGL((fwd_bf16_kernel<D, FIXED, SKIP, false, KS>), grid, dim3(kFwdThreads * KS), 0,
+                     s,
                      (const bf16*)q, (const bf16*)k, (const bf16*)v, g.ptr, qn, kn, (bf16*)o, lse,
                      BH, g.H, L, n_mblk, sl2, OutGateArgs{});
+}
+
+template <int D, bool FIXED, bool SKIP>
+static void fwd_bf16_t(const void* q, const void* k, const void* v, GateSpec g,
+                       const float* qn, const float* kn, void* o, float* lse, int BH, int L,
+                       float sl2, hipStream_t s) {
+  switch (fwd_groups<D>(BH, L)) {
+    case 4:
+      if constexpr (D == 64) {
+        fwd_bf16_k<D, FIXED, SKIP, 4>(q, k, v, g, qn, kn, o, lse, BH, L, sl2, s);
+        break;
+      }
+    case 2: fwd_bf16_k<D, FIXED, SKIP, 2>(q, k, v, g, qn, kn, o, lse, BH, L, sl2, s); break;
+    default: fwd_bf16_k<D, FIXED, SKIP, 1>(q, k, v, g, qn, kn, o, lse, BH, L, sl2, s); break;
+  }
 }
 
 template <int D, bool FIXED>
@@ -458,14 +607,28 @@ hipError_t launch_fwd_bf16(const void* q, const void* k, const void* v, GateSpec
   return hipGetLastError();
 }
 
-template <int D>
-static void fwd_bf16_outg_t(const void* q, const void* k, const void* v, const float* c, void* o,
+template <int D, int KS>
+static void fwd_bf16_outg_k(const void* q, const void* k, const void* v, const float* c, void* o,
                             float* lse, OutGateArgs og, int BH, int L, float sl2, hipStream_t s) {
   const int n_mblk = (L + kFwdBM - 1) / kFwdBM;
   const dim3 grid((unsigned)n_mblk * (unsigned)BH);
-  hipLaunchKernelGGL((fwd_bf16_kernel<D, false, false, true>), grid, dim3(kFwdThreads), 0, s,
+  hipLaunchKernelGGL((fwd_bf16_kernel<D, false, false, true, KS>), grid, dim3(kFwdThreads * KS), 0, s,
                      (const bf16*)q, (const bf16*)k, (const bf16*)v, c, nullptr, nullptr,
                      (bf16*)o, lse, BH, 1, L, n_mblk, sl2, og);
+}
+
+template <int D>
+static void fwd_bf16_outg_t(const void* q, const void* k, const void* v, const float* c, void* o,
+                            float* lse, OutGateArgs og, int BH, int L, float sl2, hipStream_t s) {
+  switch (fwd_groups<D>(BH, L)) {
+    case 4:
+      if constexpr (D == 64) {
+        fwd_bf16_outg_k<D, 4>(q, k, v, c, o, lse, og, BH, L, sl2, s);
+        break;
+      }
+    case 2: fwd_bf16_outg_k<D, 2>(q, k, v, c, o, lse, og, BH, L, sl2, s); break;
+    default: fwd_bf16_outg_k<D, 1>(q, k, v, c, o, lse, og, BH, L, sl2, s); break;
+  }
 }
 
 hipError_t launch_fwd_bf16_out_gate(const void* q, const void* k, const void* v, const float* c,
