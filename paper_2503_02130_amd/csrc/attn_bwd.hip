@@ -382,51 +382,56 @@ void bwd_dq_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
 // Each wave holds one D x 32 accumulator, so two waves fit on a SIMD, and the
 // two roles never wait for each other inside a tile: Q / dO tiles, their row
 // statistics and P are triple-buffered (tile t + 1 loads by DMA while P works
-// on t and G on t - 1), with one barrier per tile of 64 queries.  The P waves
+// on t and G on t - 1), with one barrier per tile of queries.  The P waves
 // issue all of the DMA, so the G waves never wait for vector memory.  Every LDS
 // operand address is one of a few opaque per-lane registers plus an immediate:
 // plain reads come from the tile the role multiplies from the left (Q for P,
 // dO for G) and transposing reads from the other one, so both roles share the
 // same sixteen address registers, and the loop is unrolled by three so the
 // buffer index is part of the immediate.
+//
+// Query tiles are 64 rows at D = 128 (145 KB of LDS, one workgroup per CU; 32-row
+// tiles put twice the barriers on that one workgroup, 10 % slower).  At D = 64 they
+// are 32 rows: with 51 KB of LDS and at most 128 VGPRs two workgroups share a CU, four
+// waves per SIMD, and the vector work of one (each score carries half the matrix work
+// of D = 128) runs under the products of the others.  Measured against 64-row tiles
+// and one workgroup: B H = 96, L = 2048 174 -> 148 us (storing dS 193 -> 165), B H = 32,
+// L = 8192 649 -> 532 us.  Grids that put one workgroup on a CU anyway keep 64-row
+// tiles (dkdv_short).  The sums run over the queries in the same order either way.
 // ---------------------------------------------------------------------------
 constexpr int kKvWaves = 8;
 constexpr int kKvThreads = 64 * kKvWaves;
 constexpr int kKvPairs = kKvWaves / 2;
 constexpr int kKvBN = 32 * kKvPairs;  // keys per workgroup
 static_assert(kKvBN == kRefBlock, "a dkdv workgroup's keys form one reference block");
-template <int D>
-constexpr int kv_bm() { return 64; }  // queries per tile
 
-template <int D>
+template <int D, int BM>
 struct KvSmem {
-  static constexpr int BM = kv_bm<D>();
   bf16 q[3][BM * D];
   bf16 g[3][BM * D];
   bf16x8 p[3][kKvPairs][BM / 16][64];  // P of each pair: [16-query chunk][lane], bf16 x 8
   float bq[3][BM];  // ((c_i - c_ref) - LSE_i) / s of each query row
   float dl[3][BM];  // Delta_i
-  float raw[2][3][BM];  // c_i, LSE_i, Delta_i of the next tiles as loaded (two tiles ahead)
+  float raw[2][3][64];  // c_i, LSE_i, Delta_i of the next tiles as loaded (two tiles ahead)
   int skip[3];          // the query tile and every later one contribute exact zeros
 };
 
-template <int D, bool FIXED, bool SKIP, bool STORE = false>
-__global__ __launch_bounds__(kKvThreads) void bwd_dkdv_bf16_kernel(
+template <int D, bool FIXED, bool SKIP, bool STORE, int kKvBM>
+__device__ __forceinline__ void bwd_dkdv_bf16_body(
     const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
     const float* __restrict__ gate, const float* __restrict__ qnorm,
     const float* __restrict__ knorm, const float* __restrict__ LSE, const bf16* __restrict__ dO,
     const float* __restrict__ delta, bf16* __restrict__ dK, bf16* __restrict__ dV,
     float* __restrict__ dck, bf16x8* __restrict__ ds_store, int* __restrict__ ds_tiles, int BH,
     int H, int L, float scale, float scale_log2) {
-  static_assert(!STORE || (kv_bm<D>() == 64 && kKvBN == 128 && kKvPairs == 4),
+  static_assert(!STORE || (64 % kKvBM == 0 && kKvBN == 128 && kKvPairs == 4),
                 "the stored-dS slot layout");
-  constexpr int kKvBM = kv_bm<D>();
   constexpr int NQB = kKvBM / 32;  // 32-query sub-blocks per tile
   constexpr int TILE = kKvBM * D;
-  constexpr int NDMA = TILE * 2 / 1024 / kKvWaves;
-  static_assert(NDMA >= 1 && 2 * NDMA * kKvPairs * 1024 == TILE * 2,
+  constexpr int NDMA = TILE * 2 / 1024 / kKvPairs;  // per P wave
+  static_assert(NDMA >= 1 && NDMA * kKvPairs * 1024 == TILE * 2,
                 "the P waves' DMA loads cover a tile exactly");
-  __shared__ __attribute__((aligned(16))) KvSmem<D> sm;
+  __shared__ __attribute__((aligned(16))) KvSmem<D, kKvBM> sm;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int h = lane >> 5, col = lane & 31;
@@ -508,7 +513,9 @@ __global__ __launch_bounds__(kKvThreads) void bwd_dkdv_bf16_kernel(
   float dck_part = 0.0f;
 
   const int t_first = k0 / kKvBM;
-  int n_tiles = (L + kKvBM - 1) / kKvBM - t_first;  // lowered by gate-aware skipping
+  constexpr int kPerSlot = 64 / kKvBM;  // query tiles per stored-dS slot
+  // lowered by gate-aware skipping; with STORE whole slots are written
+  int n_tiles = (STORE ? kPerSlot * ds_query_tiles(L) : (L + kKvBM - 1) / kKvBM) - t_first;
   const float skip_norm = SKIP ? 2.0f * scale * qnorm[bh] * knorm[bh] : 0.0f;
   const int k_last = min(L, k0 + kKvBN) - 1;  // the block's least decayed key
   const int t_diag = kw0 / kKvBM;  // tile holding this pair's diagonal
@@ -549,7 +556,7 @@ __global__ __launch_bounds__(kKvThreads) void bwd_dkdv_bf16_kernel(
     const uint32_t base = (uint32_t)qt * kKvBM * D * 2;
     if (pwave) {
 #pragma unroll
-      for (int i = 0; i < 2 * NDMA; ++i) {
+      for (int i = 0; i < NDMA; ++i) {
         const int wslot = (i * kKvPairs + pair) * 512;
         const uint32_t voff = dma_off + uniform_u32(base + i * tile_dma_stride<kKvPairs>());
         dma16(rq, &sm.q[B][wslot], voff);
@@ -611,11 +618,23 @@ __global__ __launch_bounds__(kKvThreads) void bwd_dkdv_bf16_kernel(
   // this block's run of stored slots (16 KB per 64-query tile, from tile t_first
   // on), for the dQ pass; non-temporal stores, the reader comes after the kernel.
   const __amdgpu_buffer_rsrc_t rds = make_rsrc(
-      STORE ? ds_store + ((size_t)bh * ds_slots_per_head(L) + ds_slot(L, nblk, t_first)) *
+      STORE ? ds_store + ((size_t)bh * ds_slots_per_head(L) + ds_slot(L, nblk, 2 * nblk)) *
                              (kDsSlotBytes / 16)
             : ds_store,
-      STORE ? (uint32_t)(ds_query_tiles(L) - t_first) * kDsSlotBytes : 0u);
+      STORE ? (uint32_t)(ds_query_tiles(L) - 2 * nblk) * kDsSlotBytes : 0u);
   const int lane16 = lane * 16;
+  // byte offset of this pair's part of query tile qt in the block's run
+  auto ds_off = [&](int qt) {
+    return (int)uniform_u32((uint32_t)((qt - t_first) / kPerSlot) * kDsSlotBytes +
+                            (uint32_t)pair * 4096u +
+                            (uint32_t)(qt % kPerSlot) * (kKvBM / 16 * 1024u));
+  };
+  auto store_zeros = [&](int qt) {
+#pragma unroll
+    for (int c = 0; c < kKvBM / 16; ++c)
+      __builtin_amdgcn_raw_buffer_store_b128(u32x4{0, 0, 0, 0}, rds, lane16, ds_off(qt) + c * 1024,
+                                             kNonTemporal);
+  };
   // G wave on tile qt held in buffer B (its P was stored in the same buffer slot)
   auto g_tile = [&](int qt, auto bufc) {
     constexpr int B = decltype(bufc)::value;
@@ -649,9 +668,7 @@ __global__ __launch_bounds__(kKvThreads) void bwd_dkdv_bf16_kernel(
         dck_part = sum8_bf16(dsb, dck_part);  // the column sums of the bf16 dS (see the dq kernel)
         if constexpr (STORE)
           __builtin_amdgcn_raw_buffer_store_b128(
-              __builtin_bit_cast(u32x4, dsb), rds, lane16,
-              (int)uniform_u32((uint32_t)(qt - t_first) * kDsSlotBytes + (uint32_t)pair * 4096u) +
-                  (2 * qb + c) * 1024,
+              __builtin_bit_cast(u32x4, dsb), rds, lane16, ds_off(qt) + (2 * qb + c) * 1024,
               kNonTemporal);
         if constexpr (SKIP) read_tr(bufc, std::integral_constant<int, 2 * qb + c>(), tr);
         lds_wait<0>(tr);
@@ -675,7 +692,8 @@ __global__ __launch_bounds__(kKvThreads) void bwd_dkdv_bf16_kernel(
     else wait_lds();
     __syncthreads();  // tile it and P of tile it - 1 are in LDS
     // tile it and all later ones add exact zeros: the G waves finish tile it - 1
-    if (SKIP && it < n_tiles && sm.skip[B]) n_tiles = it;
+    // (decided at whole slots, the granularity at which the dQ pass skips)
+    if (SKIP && it < n_tiles && it % kPerSlot == 0 && sm.skip[B]) n_tiles = it;
     if (it + 1 < n_tiles) issue_tile(t_first + it + 1, std::integral_constant<int, BN>());
     if (it + 2 < n_tiles) issue_stats(t_first + it + 2, it & 1);
     if (pwave) {
@@ -686,7 +704,11 @@ __global__ __launch_bounds__(kKvThreads) void bwd_dkdv_bf16_kernel(
       }
     } else {
       const int qt = t_first + it - 1;
-      if (it >= 1 && it <= n_tiles && qt >= t_diag) g_tile(qt, std::integral_constant<int, BP>());
+      if (it >= 1 && it <= n_tiles) {
+        if (qt >= t_diag) g_tile(qt, std::integral_constant<int, BP>());
+        // the half slot above this pair's diagonal: the dQ pass reads whole 64-query tiles
+        else if (STORE && kPerSlot > 1 && qt / kPerSlot == t_diag / kPerSlot) store_zeros(qt);
+      }
     }
     if (it + 1 < n_tiles) convert_stats(t_first + it + 1, (it + 1) & 1, std::integral_constant<int, BN>());
   };
@@ -725,7 +747,30 @@ __global__ __launch_bounds__(kKvThreads) void bwd_dkdv_bf16_kernel(
   }
   // the number of query tiles whose dS this block stored (the rest are zeros)
   if constexpr (STORE && SKIP)
-    if (tid == 0) ds_tiles[(size_t)bh * ds_key_blocks(L) + nblk] = n_tiles;
+    if (tid == 0) ds_tiles[(size_t)bh * ds_key_blocks(L) + nblk] = n_tiles / kPerSlot;
+}
+
+#define FOX_DKDV_PARAMS                                                                          \
+  const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,            \
+      const float *__restrict__ gate, const float *__restrict__ qnorm,                           \
+      const float *__restrict__ knorm, const float *__restrict__ LSE, const bf16 *__restrict__ dO, \
+      const float *__restrict__ delta, bf16 *__restrict__ dK, bf16 *__restrict__ dV,             \
+      float *__restrict__ dck, bf16x8 *__restrict__ ds_store, int *__restrict__ ds_tiles, int BH, \
+      int H, int L, float scale, float scale_log2
+#define FOX_DKDV_ARGS                                                                            \
+  Q, K, V, gate, qnorm, knorm, LSE, dO, delta, dK, dV, dck, ds_store, ds_tiles, BH, H, L, scale, \
+      scale_log2
+
+template <int D, bool FIXED, bool SKIP, bool STORE>
+__global__ __launch_bounds__(kKvThreads) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
+void bwd_dkdv_bf16_kernel(FOX_DKDV_PARAMS) {
+  bwd_dkdv_bf16_body<D, FIXED, SKIP, STORE, D == 64 ? 32 : 64>(FOX_DKDV_ARGS);
+}
+// D = 64 with 64-row query tiles, one workgroup per CU
+template <bool FIXED, bool SKIP, bool STORE>
+__global__ __launch_bounds__(kKvThreads) __attribute__((amdgpu_waves_per_eu(2)))
+void bwd_dkdv_bf16_short_kernel(FOX_DKDV_PARAMS) {
+  bwd_dkdv_bf16_body<64, FIXED, SKIP, STORE, 64>(FOX_DKDV_ARGS);
 }
 
 // ---------------------------------------------------------------------------
@@ -975,22 +1020,46 @@ hipError_t launch_bwd_delta(bool bf16_, const void* o, const void* d_o, float* d
                : launch_delta((const float*)o, (const float*)d_o, delta, BH, L, d, s);
 }
 
+// D = 64: 64-row query tiles with one workgroup per CU, or 32-row tiles with two?  With
+// one the grid takes about the longer of the longest row (L / 64 steps) and the mean
+// load, which at 512 workgroups of 256 CUs is that row; with two, everything is resident
+// but a step of a row alone takes longer.  So the line lies below 512 workgroups, and at
+// it for long rows, where a workgroup's fixed cost weighs little.  Measured (us, 64-row /
+// 32-row): 32 workgroups at L = 1000 25.4 / 27.1, 384 at L = 1000 32.1 / 33.5, 384 at
+// L = 3001 66.0 / 77.0, 512 at L = 16384 328 / 377, 512 at L = 2048 59.0 / 61.1, 512 at
+// L = 1000 38.7 / 34.2, 448 at L = 500 27.3 / 23.2, 576 at L = 3000 93.4 / 82.6, 1536 at
+// L = 2048 174 / 148.
+static bool dkdv_short(unsigned groups, int L) {
+  return groups <= 384 || (groups <= 512 && L >= 2048);
+}
+
+template <int D, bool FIXED, bool SKIP, bool STORE>
+static void dkdv_launch(const void* q, const void* k, const void* v, GateSpec g, const float* lse,
+                        const void* d_o, const float* delta, void* dk, void* dv, float* dck,
+                        void* ds_store, int* ds_tiles, int BH, int L, float scale, hipStream_t s,
+                        const float* qn, const float* kn) {
+  const dim3 grid((unsigned)((L + kKvBN - 1) / kKvBN) * (unsigned)BH);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(kKvThreads), 0, s, (const bf16*)q, (const bf16*)k,
+                       (const bf16*)v, g.ptr, qn, kn, lse, (const bf16*)d_o, delta, (bf16*)dk,
+                       (bf16*)dv, dck, (bf16x8*)ds_store, ds_tiles, BH, g.H, L, scale,
+                       scale * kLog2e);
+  };
+  if constexpr (D == 64)
+    if (dkdv_short(grid.x, L)) return launch(bwd_dkdv_bf16_short_kernel<FIXED, SKIP, STORE>);
+  launch(bwd_dkdv_bf16_kernel<D, FIXED, SKIP, STORE>);
+}
+
 template <int D, bool FIXED>
 static void dkdv_t(const void* q, const void* k, const void* v, GateSpec g, const float* lse,
                    const void* d_o, const float* delta, void* dk, void* dv, float* dck, int BH,
                    int L, float scale, hipStream_t s, const float* qn, const float* kn) {
-  const float sl2 = scale * kLog2e;
-  const dim3 grid((unsigned)((L + kKvBN - 1) / kKvBN) * (unsigned)BH);
   if (qn)
-    hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<D, FIXED, true>), grid, dim3(kKvThreads), 0, s,
-                       (const bf16*)q, (const bf16*)k, (const bf16*)v, g.ptr, qn, kn, lse,
-                       (const bf16*)d_o, delta, (bf16*)dk, (bf16*)dv, dck, nullptr, nullptr, BH,
-                       g.H, L, scale, sl2);
+    dkdv_launch<D, FIXED, true, false>(q, k, v, g, lse, d_o, delta, dk, dv, dck, nullptr, nullptr,
+                                       BH, L, scale, s, qn, kn);
   else
-    hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<D, FIXED, false>), grid, dim3(kKvThreads), 0, s,
-                       (const bf16*)q, (const bf16*)k, (const bf16*)v, g.ptr, qn, kn, lse,
-                       (const bf16*)d_o, delta, (bf16*)dk, (bf16*)dv, dck, nullptr, nullptr, BH,
-                       g.H, L, scale, sl2);
+    dkdv_launch<D, FIXED, false, false>(q, k, v, g, lse, d_o, delta, dk, dv, dck, nullptr, nullptr,
+                                        BH, L, scale, s, qn, kn);
 }
 
 hipError_t launch_bwd_dkdv(bool bf16_, const void* q, const void* k, const void* v, GateSpec g,
@@ -1086,18 +1155,6 @@ size_t bwd_stored_workspace_bytes(int BH, int L) {
   return align256(bwd_workspace_bytes(BH, L)) + stored_tail_bytes(BH, L);
 }
 
-template <int D, bool FIXED, bool SKIP>
-static void dkdv_store_t(const void* q, const void* k, const void* v, GateSpec g,
-                         const float* lse, const void* d_o, const float* delta, void* dk,
-                         void* dv, float* dck, void* ds_store, int* ds_tiles, int BH, int L,
-                         float scale, hipStream_t s, const float* qn, const float* kn) {
-  const dim3 grid((unsigned)((L + kKvBN - 1) / kKvBN) * (unsigned)BH);
-  hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<D, FIXED, SKIP, true>), grid, dim3(kKvThreads), 0, s,
-                     (const bf16*)q, (const bf16*)k, (const bf16*)v, g.ptr, qn, kn, lse,
-                     (const bf16*)d_o, delta, (bf16*)dk, (bf16*)dv, dck, (bf16x8*)ds_store,
-                     ds_tiles, BH, g.H, L, scale, scale * kLog2e);
-}
-
 template <int D>
 static void dkdv_store_d(const void* q, const void* k, const void* v, GateSpec g,
                          const float* lse, const void* d_o, const float* delta, void* dk,
@@ -1105,18 +1162,18 @@ static void dkdv_store_d(const void* q, const void* k, const void* v, GateSpec g
                          float scale, hipStream_t s, const float* qn, const float* kn) {
   if (g.fixed) {
     if (qn)
-      dkdv_store_t<D, true, true>(q, k, v, g, lse, d_o, delta, dk, dv, dck, ds_store, ds_tiles,
-                                  BH, L, scale, s, qn, kn);
+      dkdv_launch<D, true, true, true>(q, k, v, g, lse, d_o, delta, dk, dv, dck, ds_store,
+                                       ds_tiles, BH, L, scale, s, qn, kn);
     else
-      dkdv_store_t<D, true, false>(q, k, v, g, lse, d_o, delta, dk, dv, dck, ds_store, ds_tiles,
-                                   BH, L, scale, s, qn, kn);
+      dkdv_launch<D, true, false, true>(q, k, v, g, lse, d_o, delta, dk, dv, dck, ds_store,
+                                        ds_tiles, BH, L, scale, s, qn, kn);
   } else {
     if (qn)
-      dkdv_store_t<D, false, true>(q, k, v, g, lse, d_o, delta, dk, dv, dck, ds_store, ds_tiles,
-                                   BH, L, scale, s, qn, kn);
+      dkdv_launch<D, false, true, true>(q, k, v, g, lse, d_o, delta, dk, dv, dck, ds_store,
+                                        ds_tiles, BH, L, scale, s, qn, kn);
     else
-      dkdv_store_t<D, false, false>(q, k, v, g, lse, d_o, delta, dk, dv, dck, ds_store, ds_tiles,
-                                    BH, L, scale, s, qn, kn);
+      dkdv_launch<D, false, false, true>(q, k, v, g, lse, d_o, delta, dk, dv, dck, ds_store,
+                                         ds_tiles, BH, L, scale, s, qn, kn);
   }
 }
 

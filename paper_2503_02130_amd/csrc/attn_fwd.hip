@@ -105,12 +105,11 @@ __device__ __forceinline__ void group_sync(uint32_t* arrived, uint32_t target) {
 // kernel fits 128 VGPRs and runs four (the LDS would allow four workgroups per
 // CU; measured 3 % faster than three).
 template <int D, bool FIXED, bool SKIP, bool OUTG, int KS>
-__global__ __launch_bounds__(kFwdThreads * KS) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
-void fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
-                     const bf16* __restrict__ V, const float* __restrict__ gate,
-                     const float* __restrict__ qnorm, const float* __restrict__ knorm,
-                     bf16* __restrict__ O, float* __restrict__ LSE, int BH, int H, int L,
-                     int n_mblk, float scale_log2, OutGateArgs og) {
+__device__ __forceinline__ void fwd_bf16_body(
+    const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
+    const float* __restrict__ gate, const float* __restrict__ qnorm,
+    const float* __restrict__ knorm, bf16* __restrict__ O, float* __restrict__ LSE, int BH, int H,
+    int L, int n_mblk, float scale_log2, const OutGateArgs& og) {
   constexpr int TILE = kFwdBN * D;                         // bf16 elements per tile
   constexpr int NDMA = TILE * 2 / 1024 / kFwdWaves;        // 1 KB DMA loads per wave per tile
   __shared__ __attribute__((aligned(16))) FwdGroupSmem<D, KS> smem[KS];
@@ -529,6 +528,28 @@ void fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
   }
 }
 
+template <int D, bool FIXED, bool SKIP, bool OUTG>
+__global__ __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
+void fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
+                     const bf16* __restrict__ V, const float* __restrict__ gate,
+                     const float* __restrict__ qnorm, const float* __restrict__ knorm,
+                     bf16* __restrict__ O, float* __restrict__ LSE, int BH, int H, int L,
+                     int n_mblk, float scale_log2, OutGateArgs og) {
+  fwd_bf16_body<D, FIXED, SKIP, OUTG, 1>(Q, K, V, gate, qnorm, knorm, O, LSE, BH, H, L, n_mblk,
+                                         scale_log2, og);
+}
+
+template <int D, bool FIXED, bool SKIP, bool OUTG, int KS>
+__global__ __launch_bounds__(kFwdThreads * KS) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
+void fwd_bf16_split_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
+                           const bf16* __restrict__ V, const float* __restrict__ gate,
+                           const float* __restrict__ qnorm, const float* __restrict__ knorm,
+                           bf16* __restrict__ O, float* __restrict__ LSE, int BH, int H, int L,
+                           int n_mblk, float scale_log2, OutGateArgs og) {
+  fwd_bf16_body<D, FIXED, SKIP, OUTG, KS>(Q, K, V, gate, qnorm, knorm, O, LSE, BH, H, L, n_mblk,
+                                          scale_log2, og);
+}
+
 // Wave groups of a workgroup (KS): 1 where the grid fills the part, more where it does
 // not and the longest row's chain of key tiles decides the time.  The split costs a
 // merge (and at D = 128 the second, independent workgroup of a CU), so short rows and
@@ -556,39 +577,29 @@ static int fwd_groups(int BH, int L) {
   return wgs <= 512 && tiles >= 16 && 16 * tiles >= wgs ? 2 : 1;
 }
 
-template <int D, bool FIXED, bool SKIP, int KS>
-static void fwd_bf16_k(const void* q, const void* k, const void* v, GateSpec g,
-                       const float* qn, const float* kn, void* o, float* lse, int BH, int L,
-                       float sl2, hipStream_t s) {
+template <int D, bool FIXED, bool SKIP, bool OUTG>
+static void fwd_bf16_t(const void* q, const void* k, const void* v, GateSpec g,
+                       const float* qn, const float* kn, void* o, float* lse, OutGateArgs og,
+                       int BH, int L, float sl2, hipStream_t s) {
   const int n_mblk = (L + kFwdBM - 1) / kFwdBM;
   const dim3 grid((unsigned)n_mblk * (unsigned)BH);
-  hipLaunchKernelGGL((fwd_bf16_kernel<D, FIXED, SKIP, false, KS>), grid, dim3(kFwdThreads * KS), 0,
-                     s,
-                     (const bf16*)q, (const bf16*)k, (const bf16*)v, g.ptr, qn, kn, (bf16*)o, lse,
-                     BH, g.H, L, n_mblk, sl2, OutGateArgs{});
-}
-
-template <int D, bool FIXED, bool SKIP>
-static void fwd_bf16_t(const void* q, const void* k, const void* v, GateSpec g,
-                       const float* qn, const float* kn, void* o, float* lse, int BH, int L,
-                       float sl2, hipStream_t s) {
-  switch (fwd_groups<D>(BH, L)) {
-    case 4:
-      if constexpr (D == 64) {
-        fwd_bf16_k<D, FIXED, SKIP, 4>(q, k, v, g, qn, kn, o, lse, BH, L, sl2, s);
-        break;
-      }
-    case 2: fwd_bf16_k<D, FIXED, SKIP, 2>(q, k, v, g, qn, kn, o, lse, BH, L, sl2, s); break;
-    default: fwd_bf16_k<D, FIXED, SKIP, 1>(q, k, v, g, qn, kn, o, lse, BH, L, sl2, s); break;
-  }
+  auto launch = [&](auto kernel, int groups) {
+    hipLaunchKernelGGL(kernel, grid, dim3(kFwdThreads * groups), 0, s, (const bf16*)q,
+                       (const bf16*)k, (const bf16*)v, g.ptr, qn, kn, (bf16*)o, lse, BH, g.H, L,
+                       n_mblk, sl2, og);
+  };
+  const int groups = fwd_groups<D>(BH, L);
+  if (groups == 1) launch(fwd_bf16_kernel<D, FIXED, SKIP, OUTG>, 1);
+  else if (groups == 2) launch(fwd_bf16_split_kernel<D, FIXED, SKIP, OUTG, 2>, 2);
+  else if constexpr (D == 64) launch(fwd_bf16_split_kernel<D, FIXED, SKIP, OUTG, 4>, 4);
 }
 
 template <int D, bool FIXED>
 static void fwd_bf16_s(const void* q, const void* k, const void* v, GateSpec g,
                        const float* qn, const float* kn, void* o, float* lse, int BH, int L,
                        float sl2, hipStream_t s) {
-  if (qn) fwd_bf16_t<D, FIXED, true>(q, k, v, g, qn, kn, o, lse, BH, L, sl2, s);
-  else fwd_bf16_t<D, FIXED, false>(q, k, v, g, qn, kn, o, lse, BH, L, sl2, s);
+  if (qn) fwd_bf16_t<D, FIXED, true, false>(q, k, v, g, qn, kn, o, lse, {}, BH, L, sl2, s);
+  else fwd_bf16_t<D, FIXED, false, false>(q, k, v, g, qn, kn, o, lse, {}, BH, L, sl2, s);
 }
 
 hipError_t launch_fwd_bf16(const void* q, const void* k, const void* v, GateSpec g, void* o,
@@ -607,37 +618,17 @@ hipError_t launch_fwd_bf16(const void* q, const void* k, const void* v, GateSpec
   return hipGetLastError();
 }
 
-template <int D, int KS>
-static void fwd_bf16_outg_k(const void* q, const void* k, const void* v, const float* c, void* o,
-                            float* lse, OutGateArgs og, int BH, int L, float sl2, hipStream_t s) {
-  const int n_mblk = (L + kFwdBM - 1) / kFwdBM;
-  const dim3 grid((unsigned)n_mblk * (unsigned)BH);
-  hipLaunchKernelGGL((fwd_bf16_kernel<D, false, false, true, KS>), grid, dim3(kFwdThreads * KS), 0, s,
-                     (const bf16*)q, (const bf16*)k, (const bf16*)v, c, nullptr, nullptr,
-                     (bf16*)o, lse, BH, 1, L, n_mblk, sl2, og);
-}
-
-template <int D>
-static void fwd_bf16_outg_t(const void* q, const void* k, const void* v, const float* c, void* o,
-                            float* lse, OutGateArgs og, int BH, int L, float sl2, hipStream_t s) {
-  switch (fwd_groups<D>(BH, L)) {
-    case 4:
-      if constexpr (D == 64) {
-        fwd_bf16_outg_k<D, 4>(q, k, v, c, o, lse, og, BH, L, sl2, s);
-        break;
-      }
-    case 2: fwd_bf16_outg_k<D, 2>(q, k, v, c, o, lse, og, BH, L, sl2, s); break;
-    default: fwd_bf16_outg_k<D, 1>(q, k, v, c, o, lse, og, BH, L, sl2, s); break;
-  }
-}
-
 hipError_t launch_fwd_bf16_out_gate(const void* q, const void* k, const void* v, const float* c,
                                     void* o, float* lse, const void* g, const float* wo,
                                     float eps, void* y, int H, int BH, int L, int d, float scale,
                                     hipStream_t s) {
   const OutGateArgs og{static_cast<const bf16*>(g), wo, eps, static_cast<bf16*>(y), H};
-  if (d == 128) fwd_bf16_outg_t<128>(q, k, v, c, o, lse, og, BH, L, scale * kLog2e, s);
-  else fwd_bf16_outg_t<64>(q, k, v, c, o, lse, og, BH, L, scale * kLog2e, s);
+  const GateSpec gs = gate_array(c);
+  const float sl2 = scale * kLog2e;
+  if (d == 128)
+    fwd_bf16_t<128, false, false, true>(q, k, v, gs, nullptr, nullptr, o, lse, og, BH, L, sl2, s);
+  else
+    fwd_bf16_t<64, false, false, true>(q, k, v, gs, nullptr, nullptr, o, lse, og, BH, L, sl2, s);
   return hipGetLastError();
 }
 
