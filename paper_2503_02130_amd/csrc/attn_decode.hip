@@ -31,13 +31,22 @@ constexpr int kDecUnroll = 4;
 // fp32 zero, and 10 more absorb the rounding of the bound itself.
 constexpr float kSkipMargin = 160.0f;
 
+// Keys per split.  From 256 keys up, the largest split (fewer partials) that still gives
+// 2048 workgroups.  Where 256 keys leave fewer than 768 workgroups, the few there are walk
+// their keys in a chain of waits for memory, so the split goes on halving down to 32 keys
+// (one or two loads in flight per lane group), until 768 workgroups or 256 splits of a
+// sequence, beyond which the combine pass costs more than the split gains.  Measured with
+// the combine below (bf16, d = 128 unless said; us at 256 / 128 / 64 / 32 keys): B H = 16,
+// T = 4097 14.9 / 12.4 / 12.1 / 15.7 (fp32 31.2 / 20.6 / 17.9 / 19.5), T = 500 13.5 / 10.3 /
+// 9.0 / 8.0; B H = 2, T = 32768 21.6 / 19.6 / 25.2 / 41.9; above the line, B H = 128,
+// T = 2000 27.1 / 30.1 and B H = 12, T = 20000, d = 64 18.3 / 20.4.
 static int decode_keys_per_split(int BH, int T) {
-  // The largest split (fewer partials) that still gives >= 2048 workgroups.
-  for (int ks = 1024; ks >= 256; ks >>= 1) {
-    const long long wgs = (long long)BH * ((T + ks - 1) / ks);
-    if (wgs >= 2048) return ks;
-  }
-  return 256;
+  auto splits = [&](int ks) { return (long long)(T + ks - 1) / ks; };
+  for (int ks = 1024; ks > 256; ks >>= 1)
+    if (BH * splits(ks) >= 2048) return ks;
+  int ks = 256;
+  while (ks > 32 && BH * splits(ks) < 768 && splits(ks / 2) <= 256) ks >>= 1;
+  return ks;
 }
 
 int decode_num_splits(int BH, int T) {
@@ -218,22 +227,45 @@ __global__ __launch_bounds__(kDecThreads) void decode_split_kernel(
   }
 }
 
+// The splits' partials of one (batch, head): kCombineThreads / D thread groups take
+// every kCombineThreads / D-th split each (all of a thread's loads independent), the
+// maximum is found by each wave over the splits in parallel, and the groups meet in LDS.
+// One thread per element walking every split twice took most of a long, narrow step:
+// B H = 2, T = 32768 72 -> 22 us for the step at the same split.
+constexpr int kCombineThreads = 512;
 template <typename Tt, int D>
-__global__ __launch_bounds__(D) void decode_combine_kernel(
+__global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(
     const float* __restrict__ part, float* __restrict__ cc, const float* __restrict__ x_new,
     Tt* __restrict__ o, float* __restrict__ lse, int T, int n_split) {
+  constexpr int NG = kCombineThreads / D;
+  __shared__ float s_acc[NG][D];
+  __shared__ float s_l[NG];
   const int bh = blockIdx.x, tid = threadIdx.x;
+  const int g = tid / D, e = tid % D;
   const float* p = part + (size_t)bh * n_split * (D + 2);
   float M = -INFINITY;
-  for (int s = 0; s < n_split; ++s) M = fmaxf(M, p[(size_t)s * (D + 2)]);
+  for (int s = tid & 63; s < n_split; s += 64) M = fmaxf(M, p[(size_t)s * (D + 2)]);
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
   float Ls = 0.0f, acc = 0.0f;
-  for (int s = 0; s < n_split; ++s) {
+#pragma unroll 4
+  for (int s = g; s < n_split; s += NG) {
     const float* ps = p + (size_t)s * (D + 2);
     const float w = exp2_fast(ps[0] - M);
     Ls += ps[1] * w;
-    acc += ps[2 + tid] * w;
+    acc += ps[2 + e] * w;
   }
-  o[(size_t)bh * D + tid] = (Tt)(acc / Ls);
+  s_acc[g][e] = acc;
+  if (e == 0) s_l[g] = Ls;
+  __syncthreads();
+  if (g > 0) return;
+  Ls = s_l[0];
+#pragma unroll
+  for (int k = 1; k < NG; ++k) {
+    acc += s_acc[k][e];
+    Ls += s_l[k];
+  }
+  o[(size_t)bh * D + e] = (Tt)(acc / Ls);
   if (tid == 0) {
     lse[bh] = kLn2 * (M + log2f(Ls));
     if (cc) {  // append c_T to the prefix cache (data-dependent gates)
@@ -257,7 +289,7 @@ static hipError_t launch_decode_t(const void* q, const void* k_cache, const void
                      part, H, T, ks, n_split, scale * kLog2e);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((decode_combine_kernel<Tt, D>), dim3(BH), dim3(D), 0, s, part, c_cache,
+  hipLaunchKernelGGL((decode_combine_kernel<Tt, D>), dim3(BH), dim3(kCombineThreads), 0, s, part, c_cache,
                      logit_new, (Tt*)o, lse, T, n_split);
   return hipGetLastError();
 }

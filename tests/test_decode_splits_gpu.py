@@ -1,0 +1,42 @@
+"""The decode step at the edges of its split of the keys: 32 keys per split and one
+more, each finer split's limits (768 workgroups, 256 splits of a sequence), against the
+fp64 oracle; skipping bit for bit against dense; the allocation-free form bit for bit.
+
+Tolerance: the decode bars of the parity tests (bf16 relative L2 1e-2 on o, fp32 1e-4
+max-abs; LSE 1e-2 and, fp32, 1e-4 plus the rounding of the stored prefix values)."""
+import pytest
+import torch
+
+import oracle
+import paper_2503_02130_amd as fox
+from paper_2503_02130_amd import inputs
+from test_parity_gpu import check_fwd, cpu
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+CASES = ([("bf16", 128, 1, 3, T) for T in (2, 31, 32, 33, 500, 8192, 8193)] +
+         [("bf16", 64, 2, 2, T) for T in (97, 16384, 16385)] +
+         [("bf16", 64, 4, 12, 4099), ("bf16", 128, 3, 16, 4096), ("bf16", 128, 3, 16, 4097)] +
+         [("f32", 64, 1, 2, 1000), ("f32", 128, 2, 12, 1025)])
+
+
+@pytest.mark.parametrize("dtype,d,B,H,T", CASES)
+def test_decode_splits(dtype, d, B, H, T):
+    x = inputs.decode_inputs(B, H, T, d, dtype, ("normal", 3.0, 1.0), T + d, device=DEV)
+    c0 = torch.zeros((B, H, T), device=DEV)
+    c0[..., :T - 1] = fox.fox_gate_prefix(x["cached_logit"])
+    c0[..., T - 1] = float("nan")  # written, never read
+    args = (x["q"], x["k_cache"], x["v_cache"])
+    c, cs, cn = c0.clone(), c0.clone(), c0.clone()
+    o, lse = fox.fox_attn_decode(*args, c, x["logit_new"])
+    kn = fox.fox_row_norm_max(x["k_cache"])
+    os_, lses = fox.fox_attn_decode_skip(*args, cs, x["logit_new"], kn)
+    on, lsen = fox.fox_attn_decode_noalloc(*args, cn, x["logit_new"])
+    torch.cuda.synchronize()
+    for a, b, w in ((os_, lses, cs), (on, lsen, cn)):
+        assert torch.equal(a, o) and torch.equal(b, lse) and torch.equal(w, c)
+    xc = cpu(x)
+    O, LSE, cT = oracle.decode(xc["q"], xc["k_cache"], xc["v_cache"], xc["cached_logit"],
+                               xc["logit_new"], fox.default_scale(d))
+    check_fwd(dtype, o, lse, O, LSE, f"T={T}", c_abs=float(cT.abs().max()), L=T)
+    assert torch.equal(c[..., :T - 1], c0[..., :T - 1])
