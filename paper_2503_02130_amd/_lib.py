@@ -174,14 +174,27 @@ def status_string(status: int) -> str:
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    """The address as a plain int (None: NULL), which a c_void_p argument takes."""
+    return None if t is None else t.data_ptr()
 
 
 def _stream(t: torch.Tensor):
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    """The current stream's handle on t's device, without the Stream object that
+    torch.cuda.current_stream builds around it (0.1 against 1.9 us per call)."""
+    return _raw_stream(t.device.index)
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+    lambda index: torch.cuda.current_stream(index).cuda_stream)
 
 
 def _check(t: torch.Tensor, name: str, shape, dtype, device):
+    """A GPU tensor on `device` (None: any) of this shape and dtype (None: any),
+    contiguous; what passes is decided first, what is wrong named after."""
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.shape == shape
+            and (t.dtype is dtype or dtype is None)
+            and (device is None or t.device == device) and t.is_contiguous()):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.device.type != "cuda":
@@ -194,6 +207,10 @@ def _check(t: torch.Tensor, name: str, shape, dtype, device):
         raise ValueError(f"{name} must have shape {tuple(shape)} (got {tuple(t.shape)})")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
+
+
+def _workspace(nbytes: int, device) -> torch.Tensor:
+    return torch.empty(max(nbytes, 16), device=device, dtype=torch.uint8)
 
 
 def _raise(status: int, what: str):
@@ -294,9 +311,8 @@ def _attn_bwd_call(entry, ws_bytes, q, k, v, c, o, lse, d_o, scale, dq, dk, dv, 
     for name, t in (("dq", dq), ("dk", dk), ("dv", dv)):
         _check(t, name, (B, H, L, d), dt, dev)
     _check(d_log_f, "d_log_f", (B, H, L), torch.float32, dev)
-    need = ws_bytes(dt, B, H, L, d)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), device=dev, dtype=torch.uint8)
+        workspace = _workspace(ws_bytes(dt, B, H, L, d), dev)
     s = default_scale(d) if scale is None else float(scale)
     st = getattr(load(), entry)(_DT[dt], _ptr(q), _ptr(k), _ptr(v), _ptr(c), _ptr(o), _ptr(lse),
                                 _ptr(d_o), _ptr(dq), _ptr(dk), _ptr(dv), _ptr(d_log_f),
@@ -416,6 +432,48 @@ def fox_attn_bwd_dq_stored(k, ds_store, scale: Optional[float] = None, dq=None, 
     return dq, dc_q
 
 
+def _attn_bwd_logit(q, k, v, c, o, lse, gate_logit, d_o, s: float, keep_ds: bool):
+    """dq, dk, dv and d(logit) by the stages delta -> dK/dV -> dQ -> gate scan (the
+    autograd function's backward): the stages' own entry points, with the tensors they
+    share checked once and their fp32 row vectors in one allocation, since a short step
+    is bound by the host."""
+    B, H, L, d = q.shape
+    dt, dev = q.dtype, q.device
+    if dt not in _DT:
+        raise ValueError(f"unsupported dtype {dt}")
+    for name, t in (("q", q), ("k", k), ("v", v), ("o", o), ("d_o", d_o)):
+        _check(t, name, (B, H, L, d), dt, dev)
+    for name, t in (("c", c), ("lse", lse), ("gate_logit", gate_logit)):
+        _check(t, name, (B, H, L), torch.float32, dev)
+    dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
+    d_logit = torch.empty_like(c)
+    rows = (B * H * L + 3) // 4 * 4  # each vector 16-byte aligned
+    vec = torch.empty(3 * rows, device=dev, dtype=torch.float32)
+    delta = vec.data_ptr()
+    dc_q, dc_k = delta + 4 * rows, delta + 8 * rows
+    lib, st, it = load(), _stream(q), _DT[dt]
+    pq, pk, pv, pc, pl, pg = (t.data_ptr() for t in (q, k, v, c, lse, d_o))
+    _raise(lib.fox_attn_bwd_delta(it, o.data_ptr(), pg, delta, B, H, L, d, st),
+           "fox_attn_bwd_delta")
+    if keep_ds:
+        n = lib.fox_attn_bwd_ds_store_bytes(it, B, H, L, d)
+        store = torch.empty(n, device=dev, dtype=torch.uint8)
+        _raise(lib.fox_attn_bwd_dkdv_store(it, pq, pk, pv, pc, pl, pg, delta, dk.data_ptr(),
+                                           dv.data_ptr(), dc_k, store.data_ptr(), n, B, H, L, d,
+                                           s, st), "fox_attn_bwd_dkdv_store")
+        _raise(lib.fox_attn_bwd_dq_stored(it, pk, store.data_ptr(), n, dq.data_ptr(), dc_q,
+                                          B, H, L, d, s, st), "fox_attn_bwd_dq_stored")
+    else:
+        _raise(lib.fox_attn_bwd_dkdv(it, pq, pk, pv, pc, pl, pg, delta, dk.data_ptr(),
+                                     dv.data_ptr(), dc_k, B, H, L, d, s, st),
+               "fox_attn_bwd_dkdv")
+        _raise(lib.fox_attn_bwd_dq(it, pq, pk, pv, pc, pl, pg, delta, dq.data_ptr(), dc_q,
+                                   B, H, L, d, s, st), "fox_attn_bwd_dq")
+    _raise(lib.fox_dlogit_from_dc(dc_q, dc_k, gate_logit.data_ptr(), None, d_logit.data_ptr(),
+                                  B, H, L, st), "fox_dlogit_from_dc")
+    return dq, dk, dv, d_logit
+
+
 def _check_store(ds_store, dev):
     if ds_store.dtype != torch.uint8 or ds_store.dim() != 1 or not ds_store.is_contiguous():
         raise ValueError("ds_store: a contiguous 1-D uint8 tensor")
@@ -478,9 +536,8 @@ def fox_attn_decode(q, k_cache, v_cache, c_cache, gate_logit_new, scale: Optiona
     lse = torch.empty((B, H), device=dev, dtype=torch.float32) if lse is None else lse
     _check(o, "o", (B, H, d), dt, dev)
     _check(lse, "lse", (B, H), torch.float32, dev)
-    need = fox_attn_decode_workspace_bytes(dt, B, H, T, d)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), device=dev, dtype=torch.uint8)
+        workspace = _workspace(fox_attn_decode_workspace_bytes(dt, B, H, T, d), dev)
     s = default_scale(d) if scale is None else float(scale)
     st = load().fox_attn_decode(_DT[dt], _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(c_cache),
                                 _ptr(gate_logit_new), _ptr(o), _ptr(lse), _ptr(workspace),
@@ -598,9 +655,8 @@ def _bwd_fixed_call(entry, ws_bytes, q, k, v, gate_bias, o, lse, d_o, scale, dq,
         _check(d_gate_bias, "d_gate_bias", (H,), torch.float32, dev)
     else:
         d_gate_bias = None
-    need = ws_bytes(dt, B, H, L, d)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), device=dev, dtype=torch.uint8)
+        workspace = _workspace(ws_bytes(dt, B, H, L, d), dev)
     s = default_scale(d) if scale is None else float(scale)
     st = getattr(load(), entry)(_DT[dt], _ptr(q), _ptr(k), _ptr(v), _ptr(gate_bias), _ptr(o),
                                 _ptr(lse), _ptr(d_o), _ptr(dq), _ptr(dk), _ptr(dv),
@@ -628,9 +684,8 @@ def fox_attn_decode_fixed_gate(q, k_cache, v_cache, gate_bias, scale: Optional[f
     lse = torch.empty((B, H), device=dev, dtype=torch.float32) if lse is None else lse
     _check(o, "o", (B, H, d), dt, dev)
     _check(lse, "lse", (B, H), torch.float32, dev)
-    need = fox_attn_decode_workspace_bytes(dt, B, H, T, d)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), device=dev, dtype=torch.uint8)
+        workspace = _workspace(fox_attn_decode_workspace_bytes(dt, B, H, T, d), dev)
     s = default_scale(d) if scale is None else float(scale)
     st = load().fox_attn_decode_fixed_gate(_DT[dt], _ptr(q), _ptr(k_cache), _ptr(v_cache),
                                            _ptr(gate_bias), _ptr(o), _ptr(lse), _ptr(workspace),
@@ -673,9 +728,8 @@ def fox_attn_decode_skip(q, k_cache, v_cache, c_cache, gate_logit_new, k_norm_ma
     lse = torch.empty((B, H), device=dev, dtype=torch.float32) if lse is None else lse
     _check(o, "o", (B, H, d), dt, dev)
     _check(lse, "lse", (B, H), torch.float32, dev)
-    need = fox_attn_decode_workspace_bytes(dt, B, H, T, d)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), device=dev, dtype=torch.uint8)
+        workspace = _workspace(fox_attn_decode_workspace_bytes(dt, B, H, T, d), dev)
     s = default_scale(d) if scale is None else float(scale)
     st = load().fox_attn_decode_skip(_DT[dt], _ptr(q), _ptr(k_cache), _ptr(v_cache),
                                      _ptr(c_cache), _ptr(gate_logit_new), _ptr(k_norm_max),
@@ -747,9 +801,8 @@ def _bwd_skip_call(entry, ws_bytes, q, k, v, c, o, lse, d_o, q_norm_max, k_norm_
     for name, t in (("dq", dq), ("dk", dk), ("dv", dv)):
         _check(t, name, (B, H, L, d), dt, dev)
     _check(d_log_f, "d_log_f", (B, H, L), torch.float32, dev)
-    need = ws_bytes(dt, B, H, L, d)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), device=dev, dtype=torch.uint8)
+        workspace = _workspace(ws_bytes(dt, B, H, L, d), dev)
     s = default_scale(d) if scale is None else float(scale)
     st = getattr(load(), entry)(_DT[dt], _ptr(q), _ptr(k), _ptr(v), _ptr(c), _ptr(o), _ptr(lse),
                                 _ptr(d_o), _ptr(q_norm_max), _ptr(k_norm_max), _ptr(dq),
@@ -821,9 +874,8 @@ def _bwd_fixed_skip_call(entry, ws_bytes, q, k, v, gate_bias, o, lse, d_o, q_nor
     _check(k_norm_max, "k_norm_max", (B, H), torch.float32, dev)
     dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
     db = torch.empty_like(gate_bias) if want_bias_grad else None
-    need = ws_bytes(dt, B, H, L, d)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), device=dev, dtype=torch.uint8)
+        workspace = _workspace(ws_bytes(dt, B, H, L, d), dev)
     s = default_scale(d) if scale is None else float(scale)
     st = getattr(load(), entry)(_DT[dt], _ptr(q), _ptr(k), _ptr(v), _ptr(gate_bias), _ptr(o),
                                 _ptr(lse), _ptr(d_o), _ptr(q_norm_max), _ptr(k_norm_max),
@@ -851,9 +903,8 @@ def fox_attn_decode_fixed_gate_skip(q, k_cache, v_cache, gate_bias, k_norm_max,
     _check(k_norm_max, "k_norm_max", (B, H), torch.float32, dev)
     o = torch.empty_like(q) if o is None else o
     lse = torch.empty((B, H), device=dev, dtype=torch.float32) if lse is None else lse
-    need = fox_attn_decode_workspace_bytes(dt, B, H, T, d)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), device=dev, dtype=torch.uint8)
+        workspace = _workspace(fox_attn_decode_workspace_bytes(dt, B, H, T, d), dev)
     s = default_scale(d) if scale is None else float(scale)
     st = load().fox_attn_decode_fixed_gate_skip(_DT[dt], _ptr(q), _ptr(k_cache), _ptr(v_cache),
                                                 _ptr(gate_bias), _ptr(k_norm_max), _ptr(o),
@@ -918,9 +969,8 @@ def fox_pro_prologue_bwd(q_raw, k_raw, v_raw, k_shift_logit, v_shift_logit, q_no
     dqr, dkr, dvr = (torch.empty_like(q_raw) for _ in range(3))
     dka, dva = torch.empty_like(k_shift_logit), torch.empty_like(v_shift_logit)
     dwq, dwk = torch.empty_like(q_norm_weight), torch.empty_like(k_norm_weight)
-    need = fox_pro_prologue_bwd_workspace_bytes(dt, B, H, L, d)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), device=dev, dtype=torch.uint8)
+        workspace = _workspace(fox_pro_prologue_bwd_workspace_bytes(dt, B, H, L, d), dev)
     st = load().fox_pro_prologue_bwd(_DT[dt], _ptr(q_raw), _ptr(k_raw), _ptr(v_raw),
                                      _ptr(k_shift_logit), _ptr(v_shift_logit),
                                      _ptr(q_norm_weight), _ptr(k_norm_weight), float(eps),
@@ -1002,9 +1052,8 @@ def _attn_bwd_pro_call(entry, ws_bytes, q, k, v, c, o, lse, g_logit, o_norm_weig
     dq, dk, dv, dg = (torch.empty_like(q) for _ in range(4))
     dlf = torch.empty_like(c)
     dw = torch.empty_like(o_norm_weight)
-    need = ws_bytes(dt, B, H, L, d)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), device=dev, dtype=torch.uint8)
+        workspace = _workspace(ws_bytes(dt, B, H, L, d), dev)
     s = default_scale(d) if scale is None else float(scale)
     st = getattr(load(), entry)(_DT[dt], _ptr(q), _ptr(k), _ptr(v), _ptr(c), _ptr(o), _ptr(lse),
                                 _ptr(g_logit), _ptr(o_norm_weight), float(eps), _ptr(dy),
@@ -1064,9 +1113,8 @@ def fox_gate_projection_bwd(x, w_f, d_logit, want_dx=True, want_db=True, workspa
         db = torch.empty((H,), dtype=torch.float32, device=x.device)
     if db is not None:
         _check(db, "db", (H,), torch.float32, x.device)
-    need = fox_gate_projection_bwd_workspace_bytes(x.dtype, B, L, H, M)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=x.device)
+        workspace = _workspace(fox_gate_projection_bwd_workspace_bytes(x.dtype, B, L, H, M), x.device)
     st = load().fox_gate_projection_bwd(_DT[x.dtype], _ptr(x), _ptr(w_f), _ptr(d_logit), _ptr(dx),
                                         _ptr(dw), _ptr(db), _ptr(workspace), workspace.numel(),
                                         B, L, H, M, _stream(x))

@@ -35,18 +35,8 @@ class ForgettingAttention(torch.autograd.Function):
     def backward(ctx, d_o):
         q, k, v, gate_logit, c, o, lse = ctx.saved_tensors
         d_o = d_o.to(q.dtype).contiguous()
-        s = ctx.scale
-        delta = fox.fox_attn_bwd_delta(o, d_o)
-        if ctx.keep_ds:
-            B, H, L, d = q.shape
-            store = torch.empty(fox.fox_attn_bwd_ds_store_bytes(q.dtype, B, H, L, d),
-                                dtype=torch.uint8, device=q.device)
-            dk, dv, dc_k = fox.fox_attn_bwd_dkdv_store(q, k, v, c, lse, d_o, delta, store, s)
-            dq, dc_q = fox.fox_attn_bwd_dq_stored(k, store, s)
-        else:
-            dk, dv, dc_k = fox.fox_attn_bwd_dkdv(q, k, v, c, lse, d_o, delta, s)
-            dq, dc_q = fox.fox_attn_bwd_dq(q, k, v, c, lse, d_o, delta, s)
-        d_logit = fox.fox_dlogit_from_dc(dc_q, dc_k, gate_logit)
+        dq, dk, dv, d_logit = fox._attn_bwd_logit(q, k, v, c, o, lse, gate_logit, d_o, ctx.scale,
+                                                  ctx.keep_ds)
         return dq, dk, dv, d_logit, None, None
 
 
