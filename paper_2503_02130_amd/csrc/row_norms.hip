@@ -14,8 +14,15 @@
 
 namespace fox {
 
-constexpr int kNormThreads = 256;
-constexpr int kNormChunk = 1024;  // rows per workgroup (one atomic per chunk and head)
+// A workgroup takes kNormChunk rows, half as many where that leaves CUs idle; its passes
+// are a chain of waits for memory, so it is as large as it gets (one or two passes).
+// Smaller chunks for more workgroups do not pay: the chunk maxima of neighbouring heads
+// meet in one cache line, whose atomics run one after the other (1024 of them took
+// 17 us at B H = 16, L = 8192, more than reading the 33.5 MB).  Measured there 15.7 ->
+// 8.8 us against 256 threads per 1024 rows; with 512 rows 8.9 us there, 28 against 24 at
+// B H = 32, L = 16384, but 6.3 against 7.3 at B H = 2, L = 16384 (32 workgroups).
+constexpr int kNormThreads = 1024;
+constexpr int kNormChunk = 1024;
 constexpr int kNormAhead = 8;     // rows per lane group whose loads are in flight together
 
 __global__ void zero_kernel(float* __restrict__ out, int n) {
@@ -26,13 +33,14 @@ __global__ void zero_kernel(float* __restrict__ out, int n) {
 template <typename Tt, int D>
 __global__ __launch_bounds__(kNormThreads) void row_norm_max_kernel(const Tt* __restrict__ x,
                                                                     float* __restrict__ out,
-                                                                    int L, int n_chunk) {
+                                                                    int L, int n_chunk,
+                                                                    int chunk_rows) {
   constexpr int VEC = 16 / (int)sizeof(Tt);
   constexpr int LPR = D / VEC;                 // lanes per row
   constexpr int RPI = kNormThreads / LPR;      // rows per pass
   const int bh = blockIdx.x / n_chunk, chunk = blockIdx.x % n_chunk;
   const int tid = threadIdx.x, g = tid / LPR, lp = tid % LPR;
-  const int r0 = chunk * kNormChunk, r1 = min(L, r0 + kNormChunk);
+  const int r0 = chunk * chunk_rows, r1 = min(L, r0 + chunk_rows);
   const Tt* base = x + (size_t)bh * (size_t)L * D + lp * VEC;
   float best = 0.0f;
   for (int rb = r0 + g; rb < r1; rb += kNormAhead * RPI) {
@@ -69,14 +77,16 @@ __global__ __launch_bounds__(kNormThreads) void row_norm_max_kernel(const Tt* __
 
 template <typename Tt>
 static void row_norm_t(const void* x, float* out, int BH, int L, int d, hipStream_t s) {
-  const int n_chunk = (L + kNormChunk - 1) / kNormChunk;
+  const long long full = (long long)BH * ((L + kNormChunk - 1) / kNormChunk);
+  const int rows = full >= 128 ? kNormChunk : kNormChunk / 2;
+  const int n_chunk = (L + rows - 1) / rows;
   const dim3 grid((unsigned)BH * (unsigned)n_chunk);
   if (d == 128)
     hipLaunchKernelGGL((row_norm_max_kernel<Tt, 128>), grid, dim3(kNormThreads), 0, s,
-                       (const Tt*)x, out, L, n_chunk);
+                       (const Tt*)x, out, L, n_chunk, rows);
   else
     hipLaunchKernelGGL((row_norm_max_kernel<Tt, 64>), grid, dim3(kNormThreads), 0, s,
-                       (const Tt*)x, out, L, n_chunk);
+                       (const Tt*)x, out, L, n_chunk, rows);
 }
 
 hipError_t launch_row_norm_max(bool bf16_, const void* x, float* out, int BH, int L, int d,
