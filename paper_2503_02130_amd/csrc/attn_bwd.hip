@@ -1247,8 +1247,11 @@ hipError_t launch_bwd_stored(const void* q, const void* k, const void* v, const 
 }
 
 // d b^(h) = sigmoid(-b^(h)) * sum over the rows of head h and all t of d(log f):
-// one workgroup per head, a tree sum over its B rows of length L.
-constexpr int kBiasThreads = 256;
+// one workgroup per head, a tree sum over its B rows of length L.  The loads of a thread
+// are a chain of waits, so the workgroup is as large as it gets and a thread has four in
+// flight: B = 4, L = 1500 7.7 -> 4.7 us (traced) against 256 threads with one.
+constexpr int kBiasThreads = 1024;
+constexpr int kBiasAhead = 4;
 __global__ __launch_bounds__(kBiasThreads) void fixed_bias_grad_kernel(
     const float* __restrict__ dlf, const float* __restrict__ bias, float* __restrict__ dbias,
     int B, int H, int L) {
@@ -1256,7 +1259,16 @@ __global__ __launch_bounds__(kBiasThreads) void fixed_bias_grad_kernel(
   float acc = 0.0f;
   for (int b = 0; b < B; ++b) {
     const float* row = dlf + ((size_t)b * H + h) * (size_t)L;
-    for (int t = threadIdx.x; t < L; t += kBiasThreads) acc += row[t];
+    for (int t0 = threadIdx.x; t0 < L; t0 += kBiasAhead * kBiasThreads) {
+      float x[kBiasAhead];
+#pragma unroll
+      for (int u = 0; u < kBiasAhead; ++u) {
+        const int t = t0 + u * kBiasThreads;
+        x[u] = t < L ? row[t] : 0.0f;
+      }
+#pragma unroll
+      for (int u = 0; u < kBiasAhead; ++u) acc += x[u];
+    }
   }
   __shared__ float part[kBiasThreads / 64];
   for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
