@@ -373,11 +373,15 @@ __global__ __launch_bounds__(kProThreads) void out_gate_bwd_kernel(
 // dw^(h)[e] = sum over batch rows b and chunks of part[(b H + h) n_chunk + chunk][e]:
 // workgroup (h, 64 elements e); wave w sums the partials p = w, w + 4, ... in
 // order (loads unrolled for memory-level parallelism), then the four waves' sums
-// are added in order: a fixed order, so the result is deterministic.
+// are added in order: a fixed order, so the result is deterministic.  Grid z = 0, 1: two
+// gradients of one pass share the launch (about 5 us each where little else runs).
 constexpr int kReduceThreads = 256;
 __global__ __launch_bounds__(kReduceThreads) void weight_grad_reduce_kernel(
-    const float* __restrict__ part, float* __restrict__ dw, int B, int H, int n_chunk, int D) {
+    const float* __restrict__ part0, float* __restrict__ dw0, const float* __restrict__ part1,
+    float* __restrict__ dw1, int B, int H, int n_chunk, int D) {
   const int h = (int)blockIdx.x;
+  const float* part = blockIdx.z ? part1 : part0;
+  float* dw = blockIdx.z ? dw1 : dw0;
   const int e = (int)blockIdx.y * 64 + (threadIdx.x & 63);
   const int w = threadIdx.x >> 6;
   const int n = B * n_chunk;
@@ -479,11 +483,8 @@ hipError_t launch_pro_prologue_bwd(bool bf16_, const void* qr, const void* kr, c
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int B = BH / H;
-  const dim3 rgrid((unsigned)H, (unsigned)(d / 64));
-  hipLaunchKernelGGL(weight_grad_reduce_kernel, rgrid, dim3(kReduceThreads), 0, s, pwq, dwq, B,
-                     H, nc, d);
-  hipLaunchKernelGGL(weight_grad_reduce_kernel, rgrid, dim3(kReduceThreads), 0, s, pwk, dwk, B,
-                     H, nc, d);
+  hipLaunchKernelGGL(weight_grad_reduce_kernel, dim3((unsigned)H, (unsigned)(d / 64), 2),
+                     dim3(kReduceThreads), 0, s, pwq, dwq, pwk, dwk, B, H, nc, d);
   return hipGetLastError();
 }
 
@@ -546,7 +547,7 @@ hipError_t launch_bwd_pro(bool bf16_, const void* q, const void* k, const void* 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(weight_grad_reduce_kernel, dim3((unsigned)H, (unsigned)(d / 64)),
-                     dim3(kReduceThreads), 0, s, pwo, dwo, BH / H, H, nc, d);
+                     dim3(kReduceThreads), 0, s, pwo, dwo, nullptr, nullptr, BH / H, H, nc, d);
   e = hipGetLastError();
   const GateSpec gs = gate_array(c);
   if (keep_ds) {
