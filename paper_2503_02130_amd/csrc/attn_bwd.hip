@@ -80,6 +80,8 @@ __global__ __launch_bounds__(256) void bwd_delta_kernel(const T* __restrict__ O,
 // bf16 dq kernel: 128 queries per workgroup (4 waves x 32), 64-key tiles
 // double-buffered in LDS through DMA loads, diagonal tile first.  The tile loop
 // is unrolled by two so every LDS address is a per-lane base plus an immediate.
+// Short grids with long rows split the key tiles over two (D = 128) or three (D = 64)
+// groups of four waves (dq_split): B H = 16, L = 3001 97 -> 77 and 70 -> 48 us.
 // ---------------------------------------------------------------------------
 constexpr int kBwdThreads = 256;
 constexpr int kDqWaves = 4;
@@ -133,23 +135,33 @@ struct DqSmem {
   float cref[2];  // the tile's reference prefix value
   int skip[2];    // the tile and every earlier one contribute exact zeros
 };
+// With the keys split over wave groups, a group's tiles also hold its dQ partial; its
+// row sums and its barrier's count follow them.  The alignment keeps the next group's
+// tiles on 16-byte boundaries.
+template <int D, int KS>
+struct alignas(256) DqGroupSmem : DqSmem<D> {
+  float dc[kDqWaves][64];
+  uint32_t arrived;
+};
+template <int D>
+struct DqGroupSmem<D, 1> : DqSmem<D> {};
 
-// Occupancy: two waves per SIMD at D = 128; three at D = 64 (168 VGPRs; measured
-// 11 % faster than two).
-template <int D, bool FIXED, bool SKIP>
-__global__ __launch_bounds__(kBwdThreads) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2)))
-void bwd_dq_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
-                        const bf16* __restrict__ V, const float* __restrict__ gate,
-                        const float* __restrict__ qnorm, const float* __restrict__ knorm,
-                        const float* __restrict__ LSE, const bf16* __restrict__ dO,
-                        const float* __restrict__ delta, bf16* __restrict__ dQ,
-                        float* __restrict__ dcq, int BH, int H, int L, int n_mblk, float scale,
-                        float scale_log2) {
+// KS groups of four waves: group g visits key tiles t_last - g, - KS, .. with its own
+// tile buffers and barrier (group_sync), and the groups' dQ and dc^q add up in LDS.
+template <int D, bool FIXED, bool SKIP, int KS>
+__device__ __forceinline__ void bwd_dq_bf16_body(
+    const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
+    const float* __restrict__ gate, const float* __restrict__ qnorm,
+    const float* __restrict__ knorm, const float* __restrict__ LSE, const bf16* __restrict__ dO,
+    const float* __restrict__ delta, bf16* __restrict__ dQ, float* __restrict__ dcq, int BH, int H,
+    int L, int n_mblk, float scale, float scale_log2) {
   constexpr int TILE = kDqBN * D;
   constexpr int NDMA = TILE * 2 / 1024 / kDqWaves;
-  __shared__ __attribute__((aligned(16))) DqSmem<D> sm;
+  __shared__ __attribute__((aligned(16))) DqGroupSmem<D, KS> smem[KS];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = (tid >> 6) % kDqWaves;
+  const int grp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / kBwdThreads);
+  DqGroupSmem<D, KS>& sm = smem[grp];  // this group's tiles
   const int h = lane >> 5, col = lane & 31;
   // heads fastest; rotated over the XCDs when skipping (see the forward kernel)
   const int row = (int)(blockIdx.x / BH);
@@ -330,27 +342,71 @@ void bwd_dq_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
     });
   };
 
+  uint32_t arrivals = 0;
   // returns true when tile j and all earlier tiles can be skipped
   auto step = [&](int j, auto bufc) {
     constexpr int B = decltype(bufc)::value;
     wait_all_memory();
-    __syncthreads();  // tile j is in LDS; every wave is done with tile j + 1
+    // tile j is in LDS; every wave (of the group) is done with the tile before it
+    if constexpr (KS == 1) {
+      __syncthreads();
+    } else {
+      group_sync(&smem[grp].arrived, arrivals += kDqWaves);
+    }
     if (SKIP && sm.skip[B]) return true;
-    if (j > 0) issue_tile(j - 1, std::integral_constant<int, 1 - B>());
+    if (j >= KS) issue_tile(j - KS, std::integral_constant<int, 1 - B>());
     if (j == t_diag) {
       tile_body(j, bufc, std::true_type());
     } else if (j < t_diag) {
       tile_body(j, bufc, std::false_type());
     }
-    if (j > 0) store_c(j - 1, std::integral_constant<int, 1 - B>());
+    if (j >= KS) store_c(j - KS, std::integral_constant<int, 1 - B>());
     return false;
   };
 
-  issue_tile(t_last, std::integral_constant<int, 0>());
-  store_c(t_last, std::integral_constant<int, 0>());
-  for (int j = t_last; j >= 0; j -= 2) {
+  const int j0 = t_last - grp;
+  if constexpr (KS > 1) {
+    if (tid < KS) smem[tid].arrived = 0;
+    __syncthreads();
+  }
+  if (KS == 1 || j0 >= 0) {
+    issue_tile(j0, std::integral_constant<int, 0>());
+    store_c(j0, std::integral_constant<int, 0>());
+  }
+  for (int j = j0; j >= 0; j -= 2 * KS) {
     if (step(j, std::integral_constant<int, 0>())) break;
-    if (j > 0 && step(j - 1, std::integral_constant<int, 1>())) break;
+    if (j >= KS && step(j - KS, std::integral_constant<int, 1>())) break;
+  }
+
+  if constexpr (KS > 1) {
+    // groups 1.. leave each lane's dQ and dc^q in their tiles, the lanes of group 0
+    // that hold the same elements add them up
+    __syncthreads();
+    if (grp > 0) {
+      f32x4* part = reinterpret_cast<f32x4*>(&sm.k[0][0]) + wave * (D / 8) * 64 + lane;
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          part[(4 * db + g) * 64] = f32x4{dqacc[db][4 * g], dqacc[db][4 * g + 1],
+                                          dqacc[db][4 * g + 2], dqacc[db][4 * g + 3]};
+      smem[grp].dc[wave][lane] = dcq_part;
+    }
+    __syncthreads();
+    if (grp > 0) return;
+#pragma unroll
+    for (int k = 1; k < KS; ++k) {
+      const f32x4* part = reinterpret_cast<const f32x4*>(&smem[k].k[0][0]) + wave * (D / 8) * 64 + lane;
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x4 v = part[(4 * db + g) * 64];
+#pragma unroll
+          for (int jj = 0; jj < 4; ++jj) dqacc[db][4 * g + jj] += v[jj];
+        }
+      dcq_part += smem[k].dc[wave][lane];
+    }
   }
 
   const float dcq_tot = wave_sum_pair(dcq_part);
@@ -368,6 +424,32 @@ void bwd_dq_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
     }
     if (h == 0) dcq[head + qi] = dcq_tot;
   }
+}
+
+#define FOX_DQ_PARAMS                                                                            \
+  const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,            \
+      const float *__restrict__ gate, const float *__restrict__ qnorm,                           \
+      const float *__restrict__ knorm, const float *__restrict__ LSE, const bf16 *__restrict__ dO, \
+      const float *__restrict__ delta, bf16 *__restrict__ dQ, float *__restrict__ dcq, int BH,   \
+      int H, int L, int n_mblk, float scale, float scale_log2
+#define FOX_DQ_ARGS                                                                              \
+  Q, K, V, gate, qnorm, knorm, LSE, dO, delta, dQ, dcq, BH, H, L, n_mblk, scale, scale_log2
+
+// Occupancy: two waves per SIMD at D = 128; three at D = 64 (168 VGPRs; measured
+// 11 % faster than two).
+template <int D, bool FIXED, bool SKIP>
+__global__ __launch_bounds__(kBwdThreads) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2)))
+void bwd_dq_bf16_kernel(FOX_DQ_PARAMS) {
+  bwd_dq_bf16_body<D, FIXED, SKIP, 1>(FOX_DQ_ARGS);
+}
+// short grids: as many groups as fill the SIMDs of a CU with one workgroup
+template <int D>
+constexpr int kDqGroups = D == 64 ? 3 : 2;
+template <int D, bool FIXED, bool SKIP>
+__global__ __launch_bounds__(kBwdThreads * kDqGroups<D>)
+__attribute__((amdgpu_waves_per_eu(kDqGroups<D>)))
+void bwd_dq_bf16_split_kernel(FOX_DQ_PARAMS) {
+  bwd_dq_bf16_body<D, FIXED, SKIP, kDqGroups<D>>(FOX_DQ_ARGS);
 }
 
 // ---------------------------------------------------------------------------
@@ -1080,6 +1162,24 @@ hipError_t launch_bwd_dkdv(bool bf16_, const void* q, const void* k, const void*
   return hipGetLastError();
 }
 
+// Is the grid so short, and the longest row so long, that the row's chain of key tiles
+// decides the time?  Then the tiles are split over the wave groups of one workgroup per
+// CU; where the grid fills the part, several independent workgroups per CU do better.
+// Measured (graph replay, us, one group / split; workgroups x key tiles of the longest
+// row):
+//   D = 64:  64 x 8: 15.4 / 12.9     256 x 16: 25.3 / 20.7   384 x 47: 69.5 / 48.4
+//            480 x 40: 60.5 / 49.4   512 x 256: 351 / 245    512 x 16: 29.8 / 30.8
+//            576 x 24: 44.6 / 48.5   640 x 79: 120 / 120     384 x 5: 11.6 / 17.1
+//   D = 128: 64 x 8: 19.9 / 19.4     256 x 16: 35.1 / 31.5   384 x 47: 97.4 / 77.4
+//            480 x 40: 86.5 / 79.8   512 x 256: 502 / 393    512 x 16: 45.8 / 48.0
+//            576 x 47: 107 / 113     640 x 79: 176 / 178     384 x 5: 18.6 / 24.5
+// The rule takes shapes only, so that skipping and dense calls split alike.
+static bool dq_split(unsigned groups, int L) {
+  const unsigned tiles = (unsigned)(L + kDqBN - 1) / kDqBN;
+  return groups <= 512 && tiles >= 8 && 24 * tiles >= groups;
+}
+
+
 template <int D, bool FIXED>
 static void dq_t(const void* q, const void* k, const void* v, GateSpec g, const float* lse,
                  const void* d_o, const float* delta, void* dq, float* dcq, int BH, int L,
@@ -1087,14 +1187,18 @@ static void dq_t(const void* q, const void* k, const void* v, GateSpec g, const 
   const float sl2 = scale * kLog2e;
   const int n_mblk = (L + kDqBM - 1) / kDqBM;
   const dim3 grid((unsigned)n_mblk * (unsigned)BH);
-  if (qn)
-    hipLaunchKernelGGL((bwd_dq_bf16_kernel<D, FIXED, true>), grid, dim3(kBwdThreads), 0, s,
-                       (const bf16*)q, (const bf16*)k, (const bf16*)v, g.ptr, qn, kn, lse,
-                       (const bf16*)d_o, delta, (bf16*)dq, dcq, BH, g.H, L, n_mblk, scale, sl2);
-  else
-    hipLaunchKernelGGL((bwd_dq_bf16_kernel<D, FIXED, false>), grid, dim3(kBwdThreads), 0, s,
-                       (const bf16*)q, (const bf16*)k, (const bf16*)v, g.ptr, qn, kn, lse,
-                       (const bf16*)d_o, delta, (bf16*)dq, dcq, BH, g.H, L, n_mblk, scale, sl2);
+  auto launch = [&](auto kernel, int groups) {
+    hipLaunchKernelGGL(kernel, grid, dim3(kBwdThreads * groups), 0, s, (const bf16*)q,
+                       (const bf16*)k, (const bf16*)v, g.ptr, qn, kn, lse, (const bf16*)d_o, delta,
+                       (bf16*)dq, dcq, BH, g.H, L, n_mblk, scale, sl2);
+  };
+  if (dq_split(grid.x, L)) {
+    if (qn) launch(bwd_dq_bf16_split_kernel<D, FIXED, true>, kDqGroups<D>);
+    else launch(bwd_dq_bf16_split_kernel<D, FIXED, false>, kDqGroups<D>);
+  } else {
+    if (qn) launch(bwd_dq_bf16_kernel<D, FIXED, true>, 1);
+    else launch(bwd_dq_bf16_kernel<D, FIXED, false>, 1);
+  }
 }
 
 hipError_t launch_bwd_dq(bool bf16_, const void* q, const void* k, const void* v, GateSpec g,

