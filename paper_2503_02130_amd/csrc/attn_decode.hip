@@ -14,7 +14,7 @@
 // spread over all XCDs also when gate-aware skipping (below) keeps only the
 // recent splits of every sequence.
 // The lane groups of a workgroup merge through LDS into one partial per split;
-// a small second kernel merges the splits (log-sum-exp merge) and appends c_T
+// a second kernel merges the splits (log-sum-exp merge) and appends c_T
 // to the prefix cache.  Entry T-1 of that cache is never read: every workgroup
 // derives c_T itself, so the write cannot race with the readers.
 #include <mutex>
@@ -70,6 +70,70 @@ struct Vec16<float> {
   typedef f32x4 type;
   static constexpr int N = 4;
 };
+
+// A lane group's online softmax over the keys kbeg + g, + KPI, .. below kend: kDecUnroll
+// keys' loads in flight before any is used.  gate_row: the prefix cache of this (batch,
+// head); unused for fixed gates.
+template <typename Tt, int D, bool FIXED, int THREADS>
+__device__ __forceinline__ void decode_keys(const Tt* __restrict__ kh, const Tt* __restrict__ vh,
+                                            const float* __restrict__ gate_row, int T, float cT,
+                                            float lf, int kbeg, int kend, int g,
+                                            const float (&qv)[Vec16<Tt>::N], float& m, float& l,
+                                            float (&acc)[Vec16<Tt>::N]) {
+  typedef typename Vec16<Tt>::type VT;
+  constexpr int VEC = Vec16<Tt>::N;
+  constexpr int LPK = D / VEC;
+  constexpr int KPI = THREADS / LPK;
+  for (int base = kbeg; base < kend; base += KPI * kDecUnroll) {
+    VT kr[kDecUnroll], vr[kDecUnroll];
+    float cj[kDecUnroll];
+#pragma unroll
+    for (int u = 0; u < kDecUnroll; ++u) {
+      const int key = base + u * KPI + g;
+      if (key < kend) {
+        kr[u] = __builtin_nontemporal_load(reinterpret_cast<const VT*>(kh + (size_t)key * D));
+        vr[u] = __builtin_nontemporal_load(reinterpret_cast<const VT*>(vh + (size_t)key * D));
+        if constexpr (FIXED) cj[u] = (float)(key - (T - 1)) * lf * kLog2e;
+        else cj[u] = key == T - 1 ? 0.0f : (gate_row[key] - cT) * kLog2e;
+      } else {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+          kr[u][e] = (Tt)0.0f;
+          vr[u][e] = (Tt)0.0f;
+        }
+        cj[u] = INFINITY;
+      }
+    }
+    float sv[kDecUnroll];
+    float mu = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < kDecUnroll; ++u) {
+      float dot = 0.0f;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) dot += qv[e] * (float)kr[u][e];
+#pragma unroll
+      for (int off = 1; off < LPK; off <<= 1) dot += __shfl_xor(dot, off);
+      sv[u] = dot - cj[u];
+      mu = fmaxf(mu, sv[u]);
+    }
+    const float m_new = fmaxf(m, mu);
+    // A lane group with no key yet keeps m = -inf; a finite reference keeps the
+    // exponents below free of (-inf) - (-inf).
+    const float m_ref = m_new == -INFINITY ? 0.0f : m_new;
+    const float alpha = exp2_fast(m - m_ref);
+    l *= alpha;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) acc[e] *= alpha;
+#pragma unroll
+    for (int u = 0; u < kDecUnroll; ++u) {
+      const float p = exp2_fast(sv[u] - m_ref);
+      l += p;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) acc[e] += p * (float)vr[u][e];
+    }
+    m = m_new;
+  }
+}
 
 // FIXED: gate = b [H] (fixed gates, c_T - c_j = (T - 1 - j) log sigmoid(b));
 // otherwise gate = the prefix cache [BH, T] and x_new the new token's gate logit.
@@ -154,55 +218,8 @@ __global__ __launch_bounds__(kDecThreads) void decode_split_kernel(
     }
   }
 
-  for (int base = kbeg; base < kend; base += KPI * kDecUnroll) {
-    VT kr[kDecUnroll], vr[kDecUnroll];
-    float cj[kDecUnroll];
-#pragma unroll
-    for (int u = 0; u < kDecUnroll; ++u) {
-      const int key = base + u * KPI + g;
-      if (key < kend) {
-        kr[u] = __builtin_nontemporal_load(reinterpret_cast<const VT*>(kh + (size_t)key * D));
-        vr[u] = __builtin_nontemporal_load(reinterpret_cast<const VT*>(vh + (size_t)key * D));
-        if constexpr (FIXED) cj[u] = (float)(key - (T - 1)) * lf * kLog2e;
-        else cj[u] = key == T - 1 ? 0.0f : (gate[head + key] - cT) * kLog2e;
-      } else {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          kr[u][e] = (Tt)0.0f;
-          vr[u][e] = (Tt)0.0f;
-        }
-        cj[u] = INFINITY;
-      }
-    }
-    float sv[kDecUnroll];
-    float mu = -INFINITY;
-#pragma unroll
-    for (int u = 0; u < kDecUnroll; ++u) {
-      float dot = 0.0f;
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) dot += qv[e] * (float)kr[u][e];
-#pragma unroll
-      for (int off = 1; off < LPK; off <<= 1) dot += __shfl_xor(dot, off);
-      sv[u] = dot - cj[u];
-      mu = fmaxf(mu, sv[u]);
-    }
-    const float m_new = fmaxf(m, mu);
-    // A lane group with no key yet keeps m = -inf; a finite reference keeps the
-    // exponents below free of (-inf) - (-inf).
-    const float m_ref = m_new == -INFINITY ? 0.0f : m_new;
-    const float alpha = exp2_fast(m - m_ref);
-    l *= alpha;
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) acc[e] *= alpha;
-#pragma unroll
-    for (int u = 0; u < kDecUnroll; ++u) {
-      const float p = exp2_fast(sv[u] - m_ref);
-      l += p;
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) acc[e] += p * (float)vr[u][e];
-    }
-    m = m_new;
-  }
+  decode_keys<Tt, D, FIXED, kDecThreads>(kh, vh, gate + head, T, cT, lf, kbeg, kend, g, qv, m, l,
+                                         acc);
 
 #pragma unroll
   for (int e = 0; e < VEC; ++e) s_acc[g][lp * VEC + e] = acc[e];
@@ -224,6 +241,96 @@ __global__ __launch_bounds__(kDecThreads) void decode_split_kernel(
     for (int i = 0; i < KPI; ++i) Ls += s_l[i] * exp2_fast(s_m[i] - M);
     out[0] = M;
     out[1] = Ls;
+  }
+}
+
+// The whole step in one launch for short caches: one workgroup of 1024 threads per
+// (batch, head) walks all keys and writes o, lse and c_T itself.  With skipping it reads
+// every key all the same: what the bound would drop adds exact zeros.
+//
+// It pays where the keys of a head are one pass of the workgroup's loads (64 KB of keys)
+// and every workgroup has a CU.  Measured (graph replay, us, split and combine / direct):
+// bf16 B H = 16, T = 200 7.8 / 6.1 at d = 128 and T = 500 7.5 / 6.2 at d = 64 (51 and 64
+// KB), T = 500 8.2 / 10.3 at d = 128 (128 KB, two passes), fp32 T = 500 9.0 / 16.1 (256
+// KB); B H = 128, T = 200 10.2 / 8.0; B H = 1024, T = 200 23.5 / 28.7.  One launch less is
+// also 3 us less on the host.
+constexpr int kDirectThreads = 1024;
+constexpr int kDirectGroups = 256;
+template <typename Tt, int D>
+static bool decode_direct(int BH, int T) {
+  constexpr size_t kPass = (size_t)kDirectThreads * kDecUnroll * 16;
+  return BH <= kDirectGroups && (size_t)T * D * sizeof(Tt) <= kPass;
+}
+template <typename Tt, int D, bool FIXED>
+__global__ __launch_bounds__(kDirectThreads) void decode_direct_kernel(
+    const Tt* __restrict__ q, const Tt* __restrict__ kc, const Tt* __restrict__ vc,
+    const float* __restrict__ gate, const float* __restrict__ x_new, float* __restrict__ c_out,
+    Tt* __restrict__ o, float* __restrict__ lse, int H, int T, float scale_log2) {
+  typedef typename Vec16<Tt>::type VT;
+  constexpr int VEC = Vec16<Tt>::N;
+  constexpr int LPK = D / VEC;
+  constexpr int KPI = kDirectThreads / LPK;
+  constexpr int NG = kDirectThreads / D;  // thread groups of the merge, one element each
+  __shared__ float s_acc[KPI][D];
+  __shared__ float s_m[KPI], s_l[KPI];
+  const int tid = threadIdx.x, g = tid / LPK, lp = tid % LPK;
+  const int bh = blockIdx.x;
+  const size_t head = (size_t)bh * (size_t)T;
+  float cT = 0.0f, lf = 0.0f;
+  if constexpr (FIXED) {
+    lf = log_sigmoid(gate[bh % H]);
+  } else {
+    cT = (T >= 2 ? gate[head + T - 2] : 0.0f) + log_sigmoid(x_new[bh]);
+  }
+  float qv[VEC], acc[VEC];
+  const VT qq = *reinterpret_cast<const VT*>(q + (size_t)bh * D + lp * VEC);
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) {
+    qv[e] = (float)qq[e] * scale_log2;
+    acc[e] = 0.0f;
+  }
+  float m = -INFINITY, l = 0.0f;
+  decode_keys<Tt, D, FIXED, kDirectThreads>(kc + head * D + lp * VEC, vc + head * D + lp * VEC,
+                                            FIXED ? gate : gate + head, T, cT, lf, 0, T, g, qv, m,
+                                            l, acc);
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) s_acc[g][lp * VEC + e] = acc[e];
+  if (lp == 0) {
+    s_m[g] = m;
+    s_l[g] = l;
+  }
+  __syncthreads();
+  float M = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < KPI; i += 64) {
+    const int k = i + (tid & 63);
+    M = fmaxf(M, k < KPI ? s_m[k] : -INFINITY);
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
+  const int mg = tid / D, e = tid % D;
+  float ot = 0.0f, lt = 0.0f;
+#pragma unroll 4
+  for (int i = mg; i < KPI; i += NG) {
+    const float w = exp2_fast(s_m[i] - M);
+    ot += s_acc[i][e] * w;
+    lt += s_l[i] * w;
+  }
+  __syncthreads();  // every partial has been read
+  s_acc[mg][e] = ot;
+  if (e == 0) s_l[mg] = lt;
+  __syncthreads();
+  if (mg > 0) return;
+  lt = s_l[0];
+#pragma unroll
+  for (int k = 1; k < NG; ++k) {
+    ot += s_acc[k][e];
+    lt += s_l[k];
+  }
+  o[(size_t)bh * D + e] = (Tt)(ot / lt);
+  if (tid == 0) {
+    lse[bh] = kLn2 * (M + log2f(lt));
+    if constexpr (!FIXED) c_out[head + T - 1] = cT;
   }
 }
 
@@ -280,6 +387,13 @@ static hipError_t launch_decode_t(const void* q, const void* k_cache, const void
                                   const float* gate, int H, float* c_cache, const float* logit_new,
                                   const float* knorm, void* o, float* lse, void* ws, int BH, int T,
                                   float scale, hipStream_t s) {
+  if (decode_direct<Tt, D>(BH, T)) {
+    hipLaunchKernelGGL((decode_direct_kernel<Tt, D, FIXED>), dim3((unsigned)BH),
+                       dim3(kDirectThreads), 0, s, (const Tt*)q, (const Tt*)k_cache,
+                       (const Tt*)v_cache, gate, logit_new, c_cache, (Tt*)o, lse, H, T,
+                       scale * kLog2e);
+    return hipGetLastError();
+  }
   const int ks = decode_keys_per_split(BH, T);
   const int n_split = (T + ks - 1) / ks;
   float* part = static_cast<float*>(ws);

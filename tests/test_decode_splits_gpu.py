@@ -1,6 +1,7 @@
-"""The decode step at the edges of its split of the keys: 32 keys per split and one
-more, each finer split's limits (768 workgroups, 256 splits of a sequence), against the
-fp64 oracle; skipping bit for bit against dense; the allocation-free form bit for bit.
+"""The decode step at the edges of its split of the keys: one launch without a split (64
+KB of keys a head, 256 heads) and just past it, each finer split's limits (768
+workgroups, 256 splits of a sequence), against the fp64 oracle; skipping bit for bit
+against dense; the allocation-free form bit for bit.
 
 Tolerance: the decode bars of the parity tests (bf16 relative L2 1e-2 on o, fp32 1e-4
 max-abs; LSE 1e-2 and, fp32, 1e-4 plus the rounding of the stored prefix values)."""
@@ -17,7 +18,11 @@ DEV = "cuda:0"
 CASES = ([("bf16", 128, 1, 3, T) for T in (2, 31, 32, 33, 500, 8192, 8193)] +
          [("bf16", 64, 2, 2, T) for T in (97, 16384, 16385)] +
          [("bf16", 64, 4, 12, 4099), ("bf16", 128, 3, 16, 4096), ("bf16", 128, 3, 16, 4097)] +
-         [("f32", 64, 1, 2, 1000), ("f32", 128, 2, 12, 1025)])
+         [("f32", 64, 1, 2, 1000), ("f32", 128, 2, 12, 1025)] +
+         # direct and, one key or head more, split
+         [("bf16", 128, 1, 2, 256), ("bf16", 128, 1, 2, 257), ("bf16", 64, 1, 2, 512),
+          ("bf16", 64, 1, 2, 513), ("f32", 128, 1, 2, 128), ("f32", 128, 1, 2, 129),
+          ("f32", 64, 2, 2, 255), ("bf16", 128, 16, 16, 40), ("bf16", 128, 257, 1, 40)])
 
 
 @pytest.mark.parametrize("dtype,d,B,H,T", CASES)
