@@ -1072,7 +1072,7 @@ def main():
         pb = {"prologue": rows * (6 * d * e + 8), "prologue_bwd": rows * (9 * d * e + 16),
               "out_gate": rows * 3 * d * e}
         kern = {"prologue": "pro_prologue_kernel<__bf16,128>",
-                "prologue_bwd": "pro_prologue_bwd_kernel<__bf16,128>",
+                "prologue_bwd": "pro_prologue_bwd_kernel<__bf16,128,256>",
                 "out_gate": "out_gate_kernel<__bf16,128>"}
         hbm = {n: {"ms": round(rp[n], 4), "GB/s": round(b / (rp[n] * 1e-3) / 1e9, 1),
                    "frac_of_hbm_peak": round(b / (rp[n] * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),

@@ -18,7 +18,15 @@
 
 namespace fox {
 
-constexpr int kProThreads = 256;
+// Threads per workgroup.  A thread's rows are a chain of waits for memory, so the forward
+// kernels take as many threads as there are (B H = 32, L = 16384, d = 128 161 -> 152 us
+// for the prologue against 256 threads; B H = 48, L = 163, fp32 17.1 -> 11.2, the output
+// gate 12.5 -> 8.7).  The backward ones
+// hold a row's operands in registers and reduce weight gradients at the end: 512 threads
+// where every workgroup has a CU (B H = 48, L = 163, fp32 34 -> 23.5 us for the prologue's),
+// 256 with more workgroups (B H = 32, L = 4096 53 us against 57 with 512).
+constexpr int kProFwdThreads = 1024;
+constexpr int kProBwdThreads = 256, kProBwdWide = 512, kProWideGroups = 256;
 constexpr int kProRows = 256;  // rows of one (batch, head) slice per workgroup
 
 template <typename T>
@@ -71,13 +79,13 @@ __device__ __forceinline__ float inv_rms(float ss, float eps) {
 
 // Weight-gradient partials: every lane's per-element sums, reduced over the
 // row slots of the workgroup, go to part[D].
-template <int D, int VEC, int RPP>
+template <int D, int VEC, int RPP, int THREADS>
 __device__ __forceinline__ void store_weight_partial(float (*red)[D], const float (&acc)[VEC],
                                                      int slot, int part, float* out) {
 #pragma unroll
   for (int i = 0; i < VEC; ++i) red[slot][part * VEC + i] = acc[i];
   __syncthreads();
-  for (int e = threadIdx.x; e < D; e += kProThreads) {
+  for (int e = threadIdx.x; e < D; e += THREADS) {
     float s = 0.0f;
 #pragma unroll 8
     for (int r = 0; r < RPP; ++r) s += red[r][e];
@@ -90,12 +98,12 @@ __device__ __forceinline__ void store_weight_partial(float (*red)[D], const floa
 // prologue, forward
 // ---------------------------------------------------------------------------
 template <typename T, int D>
-__global__ __launch_bounds__(kProThreads) void pro_prologue_kernel(
+__global__ __launch_bounds__(kProFwdThreads) void pro_prologue_kernel(
     const T* __restrict__ qr, const T* __restrict__ kr, const T* __restrict__ vr,
     const float* __restrict__ ka, const float* __restrict__ va, const float* __restrict__ wq,
     const float* __restrict__ wk, float eps, T* __restrict__ q, T* __restrict__ k,
     T* __restrict__ v, int H, int L, int n_chunk) {
-  constexpr int VEC = ProVec<T>::N, LPR = D / VEC, RPP = kProThreads / LPR;
+  constexpr int VEC = ProVec<T>::N, LPR = D / VEC, RPP = kProFwdThreads / LPR;
   const int bh = (int)(blockIdx.x / n_chunk), chunk = (int)(blockIdx.x % n_chunk);
   const int part = threadIdx.x % LPR, slot = threadIdx.x / LPR;
   float wqv[VEC], wkv[VEC];
@@ -155,15 +163,15 @@ __global__ __launch_bounds__(kProThreads) void pro_prologue_kernel(
 //   value shift: the same with dv in place of ds and no normalisation.
 // ds_{t+1} is recomputed from row t + 1 (the neighbour rows come from the cache).
 // ---------------------------------------------------------------------------
-template <typename T, int D>
-__global__ __launch_bounds__(kProThreads) void pro_prologue_bwd_kernel(
+template <typename T, int D, int THREADS = kProBwdThreads>
+__global__ __launch_bounds__(THREADS) void pro_prologue_bwd_kernel(
     const T* __restrict__ qr, const T* __restrict__ kr, const T* __restrict__ vr,
     const float* __restrict__ ka, const float* __restrict__ va, const float* __restrict__ wq,
     const float* __restrict__ wk, float eps, const T* __restrict__ dq, const T* __restrict__ dk,
     const T* __restrict__ dv, T* __restrict__ dqr, T* __restrict__ dkr, T* __restrict__ dvr,
     float* __restrict__ dka, float* __restrict__ dva, float* __restrict__ pwq,
     float* __restrict__ pwk, int H, int L, int n_chunk) {
-  constexpr int VEC = ProVec<T>::N, LPR = D / VEC, RPP = kProThreads / LPR;
+  constexpr int VEC = ProVec<T>::N, LPR = D / VEC, RPP = THREADS / LPR;
   __shared__ float red[RPP][D];
   const int bh = (int)(blockIdx.x / n_chunk), chunk = (int)(blockIdx.x % n_chunk);
   const int part = threadIdx.x % LPR, slot = threadIdx.x / LPR;
@@ -275,8 +283,8 @@ __global__ __launch_bounds__(kProThreads) void pro_prologue_bwd_kernel(
       if (part == 0) dva[row] = b * (1.0f - b) * dl;
     }
   }
-  store_weight_partial<D, VEC, RPP>(red, aq, slot, part, pwq + (size_t)blockIdx.x * D);
-  store_weight_partial<D, VEC, RPP>(red, ak, slot, part, pwk + (size_t)blockIdx.x * D);
+  store_weight_partial<D, VEC, RPP, THREADS>(red, aq, slot, part, pwq + (size_t)blockIdx.x * D);
+  store_weight_partial<D, VEC, RPP, THREADS>(red, ak, slot, part, pwk + (size_t)blockIdx.x * D);
 }
 
 // ---------------------------------------------------------------------------
@@ -284,10 +292,10 @@ __global__ __launch_bounds__(kProThreads) void pro_prologue_bwd_kernel(
 // epilogue; this kernel serves the fp32 path and standalone use)
 // ---------------------------------------------------------------------------
 template <typename T, int D>
-__global__ __launch_bounds__(kProThreads) void out_gate_kernel(
+__global__ __launch_bounds__(kProFwdThreads) void out_gate_kernel(
     const T* __restrict__ O, const T* __restrict__ G, const float* __restrict__ wo, float eps,
     T* __restrict__ Y, int H, int L, int n_chunk) {
-  constexpr int VEC = ProVec<T>::N, LPR = D / VEC, RPP = kProThreads / LPR;
+  constexpr int VEC = ProVec<T>::N, LPR = D / VEC, RPP = kProFwdThreads / LPR;
   const int bh = (int)(blockIdx.x / n_chunk), chunk = (int)(blockIdx.x % n_chunk);
   const int part = threadIdx.x % LPR, slot = threadIdx.x / LPR;
   float w[VEC];
@@ -317,12 +325,12 @@ __global__ __launch_bounds__(kProThreads) void out_gate_kernel(
 //   Delta = rowsum(do o o) with do rounded to the storage type as the
 //   attention backward reads it.
 // ---------------------------------------------------------------------------
-template <typename T, int D>
-__global__ __launch_bounds__(kProThreads) void out_gate_bwd_kernel(
+template <typename T, int D, int THREADS = kProBwdThreads>
+__global__ __launch_bounds__(THREADS) void out_gate_bwd_kernel(
     const T* __restrict__ O, const T* __restrict__ G, const float* __restrict__ wo, float eps,
     const T* __restrict__ dY, T* __restrict__ dO, T* __restrict__ dG, float* __restrict__ delta,
     float* __restrict__ pwo, int H, int L, int n_chunk) {
-  constexpr int VEC = ProVec<T>::N, LPR = D / VEC, RPP = kProThreads / LPR;
+  constexpr int VEC = ProVec<T>::N, LPR = D / VEC, RPP = THREADS / LPR;
   __shared__ float red[RPP][D];
   const int bh = (int)(blockIdx.x / n_chunk), chunk = (int)(blockIdx.x % n_chunk);
   const int part = threadIdx.x % LPR, slot = threadIdx.x / LPR;
@@ -367,7 +375,7 @@ __global__ __launch_bounds__(kProThreads) void out_gate_bwd_kernel(
     dl = row_sum<LPR>(dl);
     if (part == 0) delta[row] = dl;
   }
-  store_weight_partial<D, VEC, RPP>(red, aw, slot, part, pwo + (size_t)blockIdx.x * D);
+  store_weight_partial<D, VEC, RPP, THREADS>(red, aw, slot, part, pwo + (size_t)blockIdx.x * D);
 }
 
 // dw^(h)[e] = sum over batch rows b and chunks of part[(b H + h) n_chunk + chunk][e]:
@@ -424,9 +432,9 @@ static void prologue_t(const void* qr, const void* kr, const void* vr, const flo
                        const float* va, const float* wq, const float* wk, float eps, void* q,
                        void* k, void* v, int H, int BH, int L, hipStream_t s) {
   const int nc = pro_chunks(L);
-  hipLaunchKernelGGL((pro_prologue_kernel<T, D>), dim3((unsigned)(BH * nc)), dim3(kProThreads), 0,
-                     s, (const T*)qr, (const T*)kr, (const T*)vr, ka, va, wq, wk, eps, (T*)q,
-                     (T*)k, (T*)v, H, L, nc);
+  hipLaunchKernelGGL((pro_prologue_kernel<T, D>), dim3((unsigned)(BH * nc)),
+                     dim3(kProFwdThreads), 0, s, (const T*)qr, (const T*)kr, (const T*)vr, ka, va,
+                     wq, wk, eps, (T*)q, (T*)k, (T*)v, H, L, nc);
 }
 
 hipError_t launch_pro_prologue(bool bf16_, const void* qr, const void* kr, const void* vr,
@@ -450,10 +458,13 @@ static void prologue_bwd_t(const void* qr, const void* kr, const void* vr, const
                            void* dvr, float* dka, float* dva, float* pwq, float* pwk, int H,
                            int BH, int L, hipStream_t s) {
   const int nc = pro_chunks(L);
-  hipLaunchKernelGGL((pro_prologue_bwd_kernel<T, D>), dim3((unsigned)(BH * nc)),
-                     dim3(kProThreads), 0, s, (const T*)qr, (const T*)kr, (const T*)vr, ka, va,
-                     wq, wk, eps, (const T*)dq, (const T*)dk, (const T*)dv, (T*)dqr, (T*)dkr,
-                     (T*)dvr, dka, dva, pwq, pwk, H, L, nc);
+  const bool wide = BH * nc <= kProWideGroups;
+  auto kern = wide ? pro_prologue_bwd_kernel<T, D, kProBwdWide> : pro_prologue_bwd_kernel<T, D>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(BH * nc)),
+                     dim3(wide ? kProBwdWide : kProBwdThreads), 0, s, (const T*)qr,
+                     (const T*)kr, (const T*)vr, ka, va, wq, wk, eps, (const T*)dq,
+                     (const T*)dk, (const T*)dv, (T*)dqr, (T*)dkr, (T*)dvr, dka, dva, pwq, pwk,
+                     H, L, nc);
 }
 
 hipError_t launch_pro_prologue_bwd(bool bf16_, const void* qr, const void* kr, const void* vr,
@@ -491,7 +502,7 @@ hipError_t launch_pro_prologue_bwd(bool bf16_, const void* qr, const void* kr, c
 hipError_t launch_out_gate(bool bf16_, const void* o, const void* g, const float* wo, float eps,
                            void* y, int H, int BH, int L, int d, hipStream_t s) {
   const int nc = pro_chunks(L);
-  const dim3 grid((unsigned)(BH * nc)), block(kProThreads);
+  const dim3 grid((unsigned)(BH * nc)), block(kProFwdThreads);
   if (bf16_) {
     if (d == 128)
       hipLaunchKernelGGL((out_gate_kernel<bf16, 128>), grid, block, 0, s, (const bf16*)o,
@@ -515,9 +526,11 @@ static void out_gate_bwd_t(const void* o, const void* g, const float* wo, float 
                            const void* dy, void* d_o, void* dg, float* delta, float* pwo, int H,
                            int BH, int L, hipStream_t s) {
   const int nc = pro_chunks(L);
-  hipLaunchKernelGGL((out_gate_bwd_kernel<T, D>), dim3((unsigned)(BH * nc)), dim3(kProThreads),
-                     0, s, (const T*)o, (const T*)g, wo, eps, (const T*)dy, (T*)d_o, (T*)dg,
-                     delta, pwo, H, L, nc);
+  const bool wide = BH * nc <= kProWideGroups;
+  auto kern = wide ? out_gate_bwd_kernel<T, D, kProBwdWide> : out_gate_bwd_kernel<T, D>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(BH * nc)),
+                     dim3(wide ? kProBwdWide : kProBwdThreads), 0, s, (const T*)o,
+                     (const T*)g, wo, eps, (const T*)dy, (T*)d_o, (T*)dg, delta, pwo, H, L, nc);
 }
 
 size_t bwd_pro_stored_workspace_bytes(int BH, int L, int d) {
