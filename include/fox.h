@@ -216,7 +216,10 @@ fox_status_t fox_dlogf_from_dc(const float* dc_q, const float* dc_k, float* d_lo
 fox_status_t fox_dlogit_from_dc(const float* dc_q, const float* dc_k, const float* gate_logit,
                        float* d_log_f, float* d_logit, int B, int H, int L, hipStream_t stream);
 
-/* Bytes of workspace fox_attn_decode needs for this shape (0 on invalid arguments). */
+/* Bytes of workspace for fox_attn_decode at this shape (0 on invalid arguments).  A
+ * smaller one that holds the partials of 256-key splits, B*H*ceil(T/256)*(d+2)*4 bytes
+ * (a workspace sized for another T, say), is taken too; the keys are then split more
+ * coarsely, which changes the order of the sums and, with few heads, costs time. */
 size_t fox_attn_decode_workspace_bytes(fox_dtype_t dtype, int B, int H, int T, int d);
 
 /*
@@ -234,7 +237,7 @@ size_t fox_attn_decode_workspace_bytes(fox_dtype_t dtype, int B, int H, int T, i
  *   gate_logit_new [B,H]     fp32 in
  *   o              [B,H,d]   dtype out
  *   lse            [B,H]     fp32 out  natural-log logsumexp of the new row
- *   workspace      device buffer of at least fox_attn_decode_workspace_bytes()
+ *   workspace      device buffer of fox_attn_decode_workspace_bytes()
  */
 fox_status_t fox_attn_decode(fox_dtype_t dtype, const void* q, const void* k_cache, const void* v_cache,
                     float* c_cache, const float* gate_logit_new, void* o, float* lse,
@@ -250,7 +253,7 @@ fox_status_t fox_attn_decode(fox_dtype_t dtype, const void* q, const void* k_cac
  * per device, on the first call with that device current).
  *
  *   Arguments, outputs and results as for fox_attn_decode (bit for bit: the same
- *   kernels, the same split plan).
+ *   kernels, the same split plan as with fox_attn_decode_workspace_bytes()).
  *   Limit: shapes whose partials exceed the array, i.e. whenever
  *   fox_attn_decode_workspace_bytes() > 64 MiB (for example B*H = 1024 heads at
  *   d = 128 with T above 129024), return FOX_ERR_TOO_LARGE and launch nothing.

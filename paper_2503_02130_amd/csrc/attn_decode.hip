@@ -17,6 +17,7 @@
 // a second kernel merges the splits (log-sum-exp merge) and appends c_T
 // to the prefix cache.  Entry T-1 of that cache is never read: every workgroup
 // derives c_T itself, so the write cannot race with the readers.
+#include <algorithm>
 #include <mutex>
 
 #include "fox_device.h"
@@ -31,6 +32,20 @@ constexpr int kDecUnroll = 4;
 // fp32 zero, and 10 more absorb the rounding of the bound itself.
 constexpr float kSkipMargin = 160.0f;
 
+constexpr int kDirectThreads = 1024;
+constexpr int kDirectGroups = 256;
+
+// One launch for the whole step (decode_direct_kernel) pays where the keys of a head are
+// one pass of the workgroup's loads (64 KB of keys) and every workgroup has a CU.  Measured (graph replay, us, split and combine / direct):
+// bf16 B H = 16, T = 200 7.8 / 6.1 at d = 128 and T = 500 7.5 / 6.2 at d = 64 (51 and 64
+// KB), T = 500 8.2 / 10.3 at d = 128 (128 KB, two passes), fp32 T = 500 9.0 / 16.1 (256
+// KB); B H = 128, T = 200 10.2 / 8.0; B H = 1024, T = 200 23.5 / 28.7.  One launch less is
+// also 3 us less on the host.
+static bool decode_direct(int BH, int T, int d, size_t elem) {
+  constexpr size_t kPass = (size_t)kDirectThreads * kDecUnroll * 16;
+  return BH <= kDirectGroups && (size_t)T * d * elem <= kPass;
+}
+
 // Keys per split.  From 256 keys up, the largest split (fewer partials) that still gives
 // 2048 workgroups.  Where 256 keys leave fewer than 768 workgroups, the few there are walk
 // their keys in a chain of waits for memory, so the split goes on halving down to 32 keys
@@ -40,22 +55,45 @@ constexpr float kSkipMargin = 160.0f;
 // T = 4097 14.9 / 12.4 / 12.1 / 15.7 (fp32 31.2 / 20.6 / 17.9 / 19.5), T = 500 13.5 / 10.3 /
 // 9.0 / 8.0; B H = 2, T = 32768 21.6 / 19.6 / 25.2 / 41.9; above the line, B H = 128,
 // T = 2000 27.1 / 30.1 and B H = 12, T = 20000, d = 64 18.3 / 20.4.
-static int decode_keys_per_split(int BH, int T) {
-  auto splits = [&](int ks) { return (long long)(T + ks - 1) / ks; };
-  for (int ks = 1024; ks > 256; ks >>= 1)
-    if (BH * splits(ks) >= 2048) return ks;
-  int ks = 256;
-  while (ks > 32 && BH * splits(ks) < 768 && splits(ks / 2) <= 256) ks >>= 1;
+//
+// A workspace that holds the partials of 256-key splits always serves: where it is too
+// small for the finer ones (sized for another length, say) the split is the finest that
+// fits.  The size a caller is told covers every finer split of up to T keys, so a
+// workspace sized for the longest cache gives each step of a growing one its own split.
+constexpr int kSplitKeys = 256, kFineGroups = 768, kFineSplits = 256, kFineKeys = 32;
+
+static int coarse_keys_per_split(int BH, int T) {
+  for (int ks = 1024; ks > kSplitKeys; ks >>= 1)
+    if (BH * (((long long)T + ks - 1) / ks) >= 2048) return ks;
+  return kSplitKeys;
+}
+
+static size_t partial_bytes(int BH, long long splits, int d) {
+  return (size_t)BH * (size_t)splits * (size_t)(d + 2) * sizeof(float);
+}
+
+static int decode_keys_per_split(int BH, int T, int d, size_t ws_bytes) {
+  auto splits = [&](int ks) { return ((long long)T + ks - 1) / ks; };
+  int ks = coarse_keys_per_split(BH, T);
+  if (ks == kSplitKeys)
+    while (ks > kFineKeys && BH * splits(ks) < kFineGroups && splits(ks / 2) <= kFineSplits &&
+           partial_bytes(BH, splits(ks / 2), d) <= ws_bytes)
+      ks >>= 1;
   return ks;
 }
 
-int decode_num_splits(int BH, int T) {
-  const int ks = decode_keys_per_split(BH, T);
-  return (T + ks - 1) / ks;
+size_t decode_min_workspace_bytes(int BH, int T, int d) {
+  const int ks = coarse_keys_per_split(BH, T);
+  return partial_bytes(BH, ((long long)T + ks - 1) / ks, d);
 }
 
-size_t decode_workspace_bytes(int BH, int T, int d) {
-  return (size_t)BH * (size_t)decode_num_splits(BH, T) * (size_t)(d + 2) * sizeof(float);
+size_t decode_workspace_bytes(bool bf16_, int BH, int T, int d) {
+  const size_t least = decode_min_workspace_bytes(BH, T, d);
+  if (decode_direct(BH, T, d, bf16_ ? 2 : 4)) return least;
+  // a split is halved below kFineGroups workgroups only, which at most doubles them
+  const long long fine = std::min({(long long)kFineSplits, 2LL * ((kFineGroups - 1) / BH),
+                                   (T + kFineKeys - 1LL) / kFineKeys});
+  return std::max(least, partial_bytes(BH, fine, d));
 }
 
 template <typename Tt>
@@ -247,20 +285,6 @@ __global__ __launch_bounds__(kDecThreads) void decode_split_kernel(
 // The whole step in one launch for short caches: one workgroup of 1024 threads per
 // (batch, head) walks all keys and writes o, lse and c_T itself.  With skipping it reads
 // every key all the same: what the bound would drop adds exact zeros.
-//
-// It pays where the keys of a head are one pass of the workgroup's loads (64 KB of keys)
-// and every workgroup has a CU.  Measured (graph replay, us, split and combine / direct):
-// bf16 B H = 16, T = 200 7.8 / 6.1 at d = 128 and T = 500 7.5 / 6.2 at d = 64 (51 and 64
-// KB), T = 500 8.2 / 10.3 at d = 128 (128 KB, two passes), fp32 T = 500 9.0 / 16.1 (256
-// KB); B H = 128, T = 200 10.2 / 8.0; B H = 1024, T = 200 23.5 / 28.7.  One launch less is
-// also 3 us less on the host.
-constexpr int kDirectThreads = 1024;
-constexpr int kDirectGroups = 256;
-template <typename Tt, int D>
-static bool decode_direct(int BH, int T) {
-  constexpr size_t kPass = (size_t)kDirectThreads * kDecUnroll * 16;
-  return BH <= kDirectGroups && (size_t)T * D * sizeof(Tt) <= kPass;
-}
 template <typename Tt, int D, bool FIXED>
 __global__ __launch_bounds__(kDirectThreads) void decode_direct_kernel(
     const Tt* __restrict__ q, const Tt* __restrict__ kc, const Tt* __restrict__ vc,
@@ -385,16 +409,16 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(
 template <typename Tt, int D, bool FIXED, bool SKIP>
 static hipError_t launch_decode_t(const void* q, const void* k_cache, const void* v_cache,
                                   const float* gate, int H, float* c_cache, const float* logit_new,
-                                  const float* knorm, void* o, float* lse, void* ws, int BH, int T,
-                                  float scale, hipStream_t s) {
-  if (decode_direct<Tt, D>(BH, T)) {
+                                  const float* knorm, void* o, float* lse, void* ws, size_t ws_bytes,
+                                  int BH, int T, float scale, hipStream_t s) {
+  if (decode_direct(BH, T, D, sizeof(Tt))) {
     hipLaunchKernelGGL((decode_direct_kernel<Tt, D, FIXED>), dim3((unsigned)BH),
                        dim3(kDirectThreads), 0, s, (const Tt*)q, (const Tt*)k_cache,
                        (const Tt*)v_cache, gate, logit_new, c_cache, (Tt*)o, lse, H, T,
                        scale * kLog2e);
     return hipGetLastError();
   }
-  const int ks = decode_keys_per_split(BH, T);
+  const int ks = decode_keys_per_split(BH, T, D, ws_bytes);
   const int n_split = (T + ks - 1) / ks;
   float* part = static_cast<float*>(ws);
   hipLaunchKernelGGL((decode_split_kernel<Tt, D, FIXED, SKIP>),
@@ -412,28 +436,29 @@ template <bool FIXED, bool SKIP>
 static hipError_t decode_dispatch(bool bf16_, const void* q, const void* k_cache,
                                   const void* v_cache, const float* gate, int H, float* c_cache,
                                   const float* logit_new, const float* knorm, void* o, float* lse,
-                                  void* ws, int BH, int T, int d, float scale, hipStream_t s) {
+                                  void* ws, size_t ws_bytes, int BH, int T, int d, float scale,
+                                  hipStream_t s) {
   if (bf16_) {
     return d == 128 ? launch_decode_t<bf16, 128, FIXED, SKIP>(q, k_cache, v_cache, gate, H,
                                                               c_cache, logit_new, knorm, o, lse,
-                                                              ws, BH, T, scale, s)
+                                                              ws, ws_bytes, BH, T, scale, s)
                     : launch_decode_t<bf16, 64, FIXED, SKIP>(q, k_cache, v_cache, gate, H,
                                                              c_cache, logit_new, knorm, o, lse,
-                                                             ws, BH, T, scale, s);
+                                                             ws, ws_bytes, BH, T, scale, s);
   }
   return d == 128 ? launch_decode_t<float, 128, FIXED, SKIP>(q, k_cache, v_cache, gate, H,
                                                              c_cache, logit_new, knorm, o, lse,
-                                                             ws, BH, T, scale, s)
+                                                             ws, ws_bytes, BH, T, scale, s)
                   : launch_decode_t<float, 64, FIXED, SKIP>(q, k_cache, v_cache, gate, H,
                                                             c_cache, logit_new, knorm, o, lse,
-                                                            ws, BH, T, scale, s);
+                                                            ws, ws_bytes, BH, T, scale, s);
 }
 
 hipError_t launch_decode(bool bf16_, const void* q, const void* k_cache, const void* v_cache,
                          float* c_cache, const float* logit_new, void* o, float* lse, void* ws,
-                         int BH, int T, int d, float scale, hipStream_t s) {
+                         size_t ws_bytes, int BH, int T, int d, float scale, hipStream_t s) {
   return decode_dispatch<false, false>(bf16_, q, k_cache, v_cache, c_cache, 1, c_cache, logit_new,
-                                       nullptr, o, lse, ws, BH, T, d, scale, s);
+                                       nullptr, o, lse, ws, ws_bytes, BH, T, d, scale, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -476,31 +501,32 @@ hipError_t launch_decode_noalloc(bool bf16_, const void* q, const void* k_cache,
                                  const void* v_cache, float* c_cache, const float* logit_new,
                                  void* o, float* lse, int BH, int T, int d, float scale,
                                  hipStream_t s) {
-  if (decode_workspace_bytes(BH, T, d) > kDecodeScratchBytes) return hipErrorInvalidValue;
+  if (decode_min_workspace_bytes(BH, T, d) > kDecodeScratchBytes) return hipErrorInvalidValue;
+  const size_t ws_bytes = kDecodeScratchBytes;
   void* ws = nullptr;
   hipError_t e = device_scratch(&ws);
   if (e != hipSuccess) return e;
   return decode_dispatch<false, false>(bf16_, q, k_cache, v_cache, c_cache, 1, c_cache, logit_new,
-                                       nullptr, o, lse, ws, BH, T, d, scale, s);
+                                       nullptr, o, lse, ws, ws_bytes, BH, T, d, scale, s);
 }
 
 hipError_t launch_decode_skip(bool bf16_, const void* q, const void* k_cache, const void* v_cache,
                               float* c_cache, const float* logit_new, const float* k_norm_max,
-                              void* o, float* lse, void* ws, int BH, int T, int d, float scale,
-                              hipStream_t s) {
+                              void* o, float* lse, void* ws, size_t ws_bytes, int BH, int T, int d,
+                              float scale, hipStream_t s) {
   return decode_dispatch<false, true>(bf16_, q, k_cache, v_cache, c_cache, 1, c_cache, logit_new,
-                                      k_norm_max, o, lse, ws, BH, T, d, scale, s);
+                                      k_norm_max, o, lse, ws, ws_bytes, BH, T, d, scale, s);
 }
 
 hipError_t launch_decode_fixed(bool bf16_, const void* q, const void* k_cache, const void* v_cache,
-                               const float* bias, int H, void* o, float* lse, void* ws, int BH,
-                               int T, int d, float scale, hipStream_t s,
+                               const float* bias, int H, void* o, float* lse, void* ws,
+                               size_t ws_bytes, int BH, int T, int d, float scale, hipStream_t s,
                                const float* k_norm_max) {
   if (k_norm_max)
     return decode_dispatch<true, true>(bf16_, q, k_cache, v_cache, bias, H, nullptr, nullptr,
-                                       k_norm_max, o, lse, ws, BH, T, d, scale, s);
+                                       k_norm_max, o, lse, ws, ws_bytes, BH, T, d, scale, s);
   return decode_dispatch<true, false>(bf16_, q, k_cache, v_cache, bias, H, nullptr, nullptr,
-                                      nullptr, o, lse, ws, BH, T, d, scale, s);
+                                      nullptr, o, lse, ws, ws_bytes, BH, T, d, scale, s);
 }
 
 }  // namespace fox

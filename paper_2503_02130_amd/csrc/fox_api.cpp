@@ -277,7 +277,7 @@ fox_status_t fox_dlogit_from_dc(const float* dc_q, const float* dc_k, const floa
 
 size_t fox_attn_decode_workspace_bytes(fox_dtype_t dtype, int B, int H, int T, int d) {
   if (check_dims(B, H, T, d) || check_dtype_d(dtype, d)) return 0;
-  return fox::decode_workspace_bytes(B * H, T, d);
+  return fox::decode_workspace_bytes(dtype == FOX_DTYPE_BF16, B * H, T, d);
 }
 
 fox_status_t fox_attn_decode(fox_dtype_t dtype, const void* q, const void* k_cache, const void* v_cache,
@@ -293,11 +293,12 @@ fox_status_t fox_attn_decode(fox_dtype_t dtype, const void* q, const void* k_cac
   if (!aligned16(q) || !aligned16(k_cache) || !aligned16(v_cache) || !aligned16(c_cache) ||
       !aligned16(gate_logit_new) || !aligned16(o) || !aligned16(lse))
     return FOX_ERR_ALIGN;
-  if (!workspace || workspace_bytes < fox::decode_workspace_bytes(B * H, T, d))
+  if (!workspace || workspace_bytes < fox::decode_min_workspace_bytes(B * H, T, d))
     return FOX_ERR_WORKSPACE;
   if (!aligned16(workspace)) return FOX_ERR_ALIGN;
   return launch_status(fox::launch_decode(dtype == FOX_DTYPE_BF16, q, k_cache, v_cache, c_cache,
-                                          gate_logit_new, o, lse, workspace, B * H, T, d, scale,
+                                          gate_logit_new, o, lse, workspace, workspace_bytes,
+                                          B * H, T, d, scale,
                                           static_cast<hipStream_t>(stream)));
 }
 
@@ -314,7 +315,7 @@ fox_status_t fox_attn_decode_noalloc(fox_dtype_t dtype, const void* q, const voi
   if (!aligned16(q) || !aligned16(k_cache) || !aligned16(v_cache) || !aligned16(c_cache) ||
       !aligned16(gate_logit_new) || !aligned16(o) || !aligned16(lse))
     return FOX_ERR_ALIGN;
-  if (fox::decode_workspace_bytes(B * H, T, d) > fox::kDecodeScratchBytes)
+  if (fox::decode_min_workspace_bytes(B * H, T, d) > fox::kDecodeScratchBytes)
     return FOX_ERR_TOO_LARGE;
   return launch_status(fox::launch_decode_noalloc(dtype == FOX_DTYPE_BF16, q, k_cache, v_cache,
                                                   c_cache, gate_logit_new, o, lse, B * H, T, d,
@@ -415,12 +416,12 @@ fox_status_t fox_attn_decode_skip(fox_dtype_t dtype, const void* q, const void* 
   if (!aligned16(q) || !aligned16(k_cache) || !aligned16(v_cache) || !aligned16(c_cache) ||
       !aligned16(gate_logit_new) || !aligned16(k_norm_max) || !aligned16(o) || !aligned16(lse))
     return FOX_ERR_ALIGN;
-  if (!workspace || workspace_bytes < fox::decode_workspace_bytes(B * H, T, d))
+  if (!workspace || workspace_bytes < fox::decode_min_workspace_bytes(B * H, T, d))
     return FOX_ERR_WORKSPACE;
   if (!aligned16(workspace)) return FOX_ERR_ALIGN;
   return launch_status(fox::launch_decode_skip(dtype == FOX_DTYPE_BF16, q, k_cache, v_cache,
                                                c_cache, gate_logit_new, k_norm_max, o, lse,
-                                               workspace, B * H, T, d, scale,
+                                               workspace, workspace_bytes, B * H, T, d, scale,
                                                static_cast<hipStream_t>(stream)));
 }
 
@@ -549,12 +550,12 @@ fox_status_t fox_attn_decode_fixed_gate(fox_dtype_t dtype, const void* q, const 
   if (!aligned16(q) || !aligned16(k_cache) || !aligned16(v_cache) || !aligned16(gate_bias) ||
       !aligned16(o) || !aligned16(lse))
     return FOX_ERR_ALIGN;
-  if (!workspace || workspace_bytes < fox::decode_workspace_bytes(B * H, T, d))
+  if (!workspace || workspace_bytes < fox::decode_min_workspace_bytes(B * H, T, d))
     return FOX_ERR_WORKSPACE;
   if (!aligned16(workspace)) return FOX_ERR_ALIGN;
   return launch_status(fox::launch_decode_fixed(dtype == FOX_DTYPE_BF16, q, k_cache, v_cache,
-                                                gate_bias, H, o, lse, workspace, B * H, T, d, scale,
-                                                static_cast<hipStream_t>(stream)));
+                                                gate_bias, H, o, lse, workspace, workspace_bytes,
+                                                B * H, T, d, scale, static_cast<hipStream_t>(stream)));
 }
 
 fox_status_t fox_attn_fwd_fixed_gate_skip(fox_dtype_t dtype, const void* q, const void* k, const void* v,
@@ -612,12 +613,12 @@ fox_status_t fox_attn_decode_fixed_gate_skip(fox_dtype_t dtype, const void* q, c
   st = check_dtype_d(dtype, d);
   if (st) return st;
   if (!all_aligned16({q, k_cache, v_cache, gate_bias, k_norm_max, o, lse})) return FOX_ERR_ALIGN;
-  if (!workspace || workspace_bytes < fox::decode_workspace_bytes(B * H, T, d))
+  if (!workspace || workspace_bytes < fox::decode_min_workspace_bytes(B * H, T, d))
     return FOX_ERR_WORKSPACE;
   if (!aligned16(workspace)) return FOX_ERR_ALIGN;
   return launch_status(fox::launch_decode_fixed(dtype == FOX_DTYPE_BF16, q, k_cache, v_cache,
-                                                gate_bias, H, o, lse, workspace, B * H, T, d,
-                                                scale, static_cast<hipStream_t>(stream),
+                                                gate_bias, H, o, lse, workspace, workspace_bytes,
+                                                B * H, T, d, scale, static_cast<hipStream_t>(stream),
                                                 k_norm_max));
 }
 

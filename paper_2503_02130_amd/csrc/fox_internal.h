@@ -105,8 +105,10 @@ hipError_t launch_bwd_fixed(bool bf16, const void* q, const void* k, const void*
 hipError_t launch_row_norm_max(bool bf16, const void* x, float* out, int BH, int L, int d,
                                hipStream_t s);
 
-int decode_num_splits(int BH, int T);
-size_t decode_workspace_bytes(int BH, int T, int d);
+// The workspace a decode call is told to bring, and the least it is accepted with (the
+// partials of 256-key splits; with less than the former the splits are coarser).
+size_t decode_workspace_bytes(bool bf16, int BH, int T, int d);
+size_t decode_min_workspace_bytes(int BH, int T, int d);
 // the allocation-free decode: its split partials in a file-scope device array of
 // this many bytes (per device); shapes needing more are rejected
 constexpr size_t kDecodeScratchBytes = size_t(64) << 20;
@@ -116,18 +118,18 @@ hipError_t launch_decode_noalloc(bool bf16, const void* q, const void* k_cache,
                                  hipStream_t s);
 hipError_t launch_decode(bool bf16, const void* q, const void* k_cache, const void* v_cache,
                          float* c_cache, const float* logit_new, void* o, float* lse, void* ws,
-                         int BH, int T, int d, float scale, hipStream_t s);
+                         size_t ws_bytes, int BH, int T, int d, float scale, hipStream_t s);
 // Exact gate-aware skipping (k_norm_max [BH] from launch_row_norm_max over the
 // whole cache): a split whose every score lies more than 160 (base 2) below the
 // new token's own score is not read; its merge weight would underflow to 0.
 hipError_t launch_decode_skip(bool bf16, const void* q, const void* k_cache, const void* v_cache,
                               float* c_cache, const float* logit_new, const float* k_norm_max,
-                              void* o, float* lse, void* ws, int BH, int T, int d, float scale,
-                              hipStream_t s);
+                              void* o, float* lse, void* ws, size_t ws_bytes, int BH, int T, int d,
+                              float scale, hipStream_t s);
 // Fixed gates: no prefix cache; bias [H]; with k_norm_max, exact skipping as above.
 hipError_t launch_decode_fixed(bool bf16, const void* q, const void* k_cache, const void* v_cache,
-                               const float* bias, int H, void* o, float* lse, void* ws, int BH,
-                               int T, int d, float scale, hipStream_t s,
+                               const float* bias, int H, void* o, float* lse, void* ws,
+                               size_t ws_bytes, int BH, int T, int d, float scale, hipStream_t s,
                                const float* k_norm_max = nullptr);
 
 // FoX (Pro) prologue and epilogue (pro_fusions.hip).  Weights [H, d] fp32; shift

@@ -45,3 +45,31 @@ def test_decode_splits(dtype, d, B, H, T):
                                xc["logit_new"], fox.default_scale(d))
     check_fwd(dtype, o, lse, O, LSE, f"T={T}", c_abs=float(cT.abs().max()), L=T)
     assert torch.equal(c[..., :T - 1], c0[..., :T - 1])
+
+
+@pytest.mark.parametrize("B,H,T,Tmax", [(1, 2, 8193, 8193), (1, 3, 500, 9000), (2, 8, 6000, 8192),
+                                        (2, 8, 4097, 4097), (1, 16, 47 * 128, 48 * 128)])
+def test_decode_other_workspaces(B, H, T, Tmax):
+    """The workspace of 256-key splits alone (coarser splits: the oracle bars; bytes past
+    it untouched), and one sized for a longer cache (the same splits, bit for bit)."""
+    d = 128
+    x = inputs.decode_inputs(B, H, T, d, "bf16", ("normal", 3.0, 1.0), T + H, device=DEV)
+    c = torch.zeros((B, H, T), device=DEV)
+    c[..., :T - 1] = fox.fox_gate_prefix(x["cached_logit"])
+    args = (x["q"], x["k_cache"], x["v_cache"], c, x["logit_new"])
+    o, lse = fox.fox_attn_decode(*args)
+    need = fox.fox_attn_decode_workspace_bytes(torch.bfloat16, B, H, Tmax, d)
+    assert need >= fox.fox_attn_decode_workspace_bytes(torch.bfloat16, B, H, T, d)
+    ol, lsel = fox.fox_attn_decode(*args, workspace=torch.empty(need, dtype=torch.uint8,
+                                                                device=DEV))
+    assert torch.equal(ol, o) and torch.equal(lsel, lse)
+    least = B * H * -(-T // 256) * (d + 2) * 4
+    room = torch.full((least + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+    os_, lses = fox.fox_attn_decode(*args, workspace=room[:least])
+    assert bool((room[least:] == 0xA5).all())
+    with pytest.raises(fox.FoxError):
+        fox.fox_attn_decode(*args, workspace=room[:least - 4])
+    xc = cpu(x)
+    O, LSE, cT = oracle.decode(xc["q"], xc["k_cache"], xc["v_cache"], xc["cached_logit"],
+                               xc["logit_new"], fox.default_scale(d))
+    check_fwd("bf16", os_, lses, O, LSE, f"T={T}", c_abs=float(cT.abs().max()), L=T)
