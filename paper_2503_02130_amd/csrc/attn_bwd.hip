@@ -164,8 +164,9 @@ __device__ __forceinline__ void bwd_dq_bf16_body(
   DqGroupSmem<D, KS>& sm = smem[grp];  // this group's tiles
   const int h = lane >> 5, col = lane & 31;
   // heads fastest; rotated over the XCDs when skipping (see the forward kernel)
-  const int row = (int)(blockIdx.x / BH);
-  const int bh = SKIP ? (int)((blockIdx.x + row) % BH) : (int)(blockIdx.x % BH);
+  const int bid = KS == 1 && !SKIP ? paired_block() : (int)blockIdx.x;
+  const int row = bid / BH;
+  const int bh = SKIP ? (bid + row) % BH : bid % BH;
   const int mblk = n_mblk - 1 - row;
   const int q0 = mblk * kDqBM;
   const size_t head = (size_t)bh * (size_t)L;

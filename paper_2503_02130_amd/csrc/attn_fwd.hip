@@ -110,8 +110,9 @@ __device__ __forceinline__ void fwd_bf16_body(
   const int h = lane >> 5, col = lane & 31;
   // heads fastest (a head's blocks on one XCD, sharing its L2); with skipping the
   // work per head depends on its gates, so the heads rotate over the XCDs
-  const int row = (int)(blockIdx.x / BH);
-  const int bh = SKIP ? (int)((blockIdx.x + row) % BH) : (int)(blockIdx.x % BH);
+  const int bid = KS == 1 && !SKIP ? paired_block() : (int)blockIdx.x;
+  const int row = bid / BH;
+  const int bh = SKIP ? (bid + row) % BH : bid % BH;
   const int mblk = n_mblk - 1 - row;
   const int q0 = mblk * kFwdBM;
   const size_t head = (size_t)bh * (size_t)L;

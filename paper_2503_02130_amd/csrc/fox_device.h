@@ -391,4 +391,24 @@ __device__ __forceinline__ bf16x8 tile_tr_operand(const bf16* tile, const int (&
   return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
+// The place of a workgroup in a grid sorted by falling work, for kernels with two or more
+// workgroups per CU.  An empty part takes workgroups 0-255 one per CU and then 256-511 in
+// the same order (measured), so the heaviest of each pass would share a CU; reversing the
+// second pass pairs heavy with light.  Groups of eight keep their order, so that a head
+// keeps its XCD.  Measured (graph replay, us, in order / paired; workgroups):
+//   forward, D = 128: 512 21.4 / 20.6, 768 56.8 / 54.2, 1024 (16 heads) 281 / 268, 1024
+//     (32 heads) 152 / 147, 2048 507 / 506; D = 64: 768 25.8 / 23.8, 1536 67.7 / 67.3
+//   dQ, D = 128: 768 74.1 / 72.4, 1024 407 / 392, 2048 758 / 753; D = 64: 768 35.4 / 33.7
+// Past 2048 workgroups the first passes are too small a part to matter.  With one workgroup
+// per CU the second pass goes to whichever CU is free first, and falling work is the right
+// order (512 workgroups of the split forward 52.9 / 59.4, of the split dQ 68.9 / 79.6).
+// Skipping calls, whose work does not fall with the place alone, keep their order (forward
+// with 1024 workgroups 126 / 135 or 225 / 217, by the heads' gates).
+__device__ __forceinline__ int paired_block() {
+  const int id = (int)blockIdx.x, k = id - 256;
+  if (k < 0 || k >= 256 || gridDim.x > 2048) return id;
+  const int full = min(256, (int)gridDim.x - 256) & ~7;
+  return k < full ? 256 + full - 8 - (k & ~7) + (k & 7) : id;
+}
+
 }  // namespace fox
