@@ -71,6 +71,14 @@ __device__ __forceinline__ void load_w(const float* p, float (&w)[N]) {
 
 __device__ __forceinline__ float sigmoid(float x) { return 1.0f / (1.0f + expf(-x)); }
 
+// One element of a token shift, m p + m1 x (p the row before, m1 = 1 - m).  Which product is
+// rounded before the sum is written out: left to the compiler, it changes with the launch
+// shape and the type (1024 threads flipped the bf16 value shift, 512 the backward's
+// recomputed key row), and the last bits with it.
+__device__ __forceinline__ float shift_mix(float m, float p, float m1, float x) {
+  return fmaf(m, p, m1 * x);
+}
+
 // 1 / sqrt(mean of squares + eps) of one row, from each lane's partial sum of squares
 template <int LPR, int D>
 __device__ __forceinline__ float inv_rms(float ss, float eps) {
@@ -140,7 +148,7 @@ __global__ __launch_bounds__(kProFwdThreads) void pro_prologue_kernel(
     ss = 0.0f;
 #pragma unroll
     for (int i = 0; i < VEC; ++i) {
-      xk[i] = a * pk[i] + a1 * xk[i];
+      xk[i] = shift_mix(a, pk[i], a1, xk[i]);
       ss += xk[i] * xk[i];
     }
     r = inv_rms<LPR, D>(ss, eps);
@@ -149,7 +157,7 @@ __global__ __launch_bounds__(kProFwdThreads) void pro_prologue_kernel(
     store_vec<T>(k + off, xk);
     // v = b v~_{t-1} + (1 - b) v~_t
 #pragma unroll
-    for (int i = 0; i < VEC; ++i) xv[i] = b * pv[i] + b1 * xv[i];
+    for (int i = 0; i < VEC; ++i) xv[i] = shift_mix(b, pv[i], b1, xv[i]);
     store_vec<T>(v + off, xv);
   }
 }
@@ -253,12 +261,12 @@ __global__ __launch_bounds__(THREADS) void pro_prologue_bwd_kernel(
     {
       float sn[VEC], ds[VEC], dsn[VEC];
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) sn[i] = a * kp[i] + (1.0f - a) * kc[i];
+      for (int i = 0; i < VEC; ++i) sn[i] = shift_mix(a, kp[i], 1.0f - a, kc[i]);
       norm_bwd(sn, gk, ds);
 #pragma unroll
       for (int i = 0; i < VEC; ++i) ak[i] += gk[i] * sn[i];
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) sn[i] = an * kc[i] + (1.0f - an) * kn[i];
+      for (int i = 0; i < VEC; ++i) sn[i] = shift_mix(an, kc[i], 1.0f - an, kn[i]);
       norm_bwd(sn, gkn, dsn);
       float dl = 0.0f;
 #pragma unroll
