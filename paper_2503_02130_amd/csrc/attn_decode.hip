@@ -159,15 +159,17 @@ __device__ __forceinline__ void decode_keys(const Tt* __restrict__ kh, const Tt*
     // exponents below free of (-inf) - (-inf).
     const float m_ref = m_new == -INFINITY ? 0.0f : m_new;
     const float alpha = exp2_fast(m - m_ref);
-    l *= alpha;
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) acc[e] *= alpha;
+    // The first key's product is rounded and the old sum scaled within the fma: written out,
+    // since the compiler's choice between the two changes with the code around it.
 #pragma unroll
     for (int u = 0; u < kDecUnroll; ++u) {
       const float p = exp2_fast(sv[u] - m_ref);
-      l += p;
+      l = u == 0 ? fmaf(alpha, l, p) : l + p;
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) acc[e] += p * (float)vr[u][e];
+      for (int e = 0; e < VEC; ++e) {
+        const float v = (float)vr[u][e];
+        acc[e] = u == 0 ? fmaf(alpha, acc[e], p * v) : fmaf(p, v, acc[e]);
+      }
     }
     m = m_new;
   }

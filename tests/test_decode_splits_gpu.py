@@ -73,3 +73,36 @@ def test_decode_other_workspaces(B, H, T, Tmax):
     O, LSE, cT = oracle.decode(xc["q"], xc["k_cache"], xc["v_cache"], xc["cached_logit"],
                                xc["logit_new"], fox.default_scale(d))
     check_fwd("bf16", os_, lses, O, LSE, f"T={T}", c_abs=float(cT.abs().max()), L=T)
+
+
+def test_decode_rounding():
+    """The running sum's rounding, acc <- fma(alpha, acc, rn(p v)) for the first key of a
+    pass of the loads and fma(p, v, acc) for the others, checked bit for bit on two passes
+    of one lane group: q = 0 and prefix values that make p = 1 and alpha = 2^-x, so that o
+    follows from v, alpha and fp32 arithmetic.  alpha itself is the hardware's exponential:
+    some value within 2 ulp must explain every element."""
+    H, T, d = 768, 128, 64  # no direct launch, one split, two passes of 4 x 16 keys
+    g = torch.Generator(DEV).manual_seed(3)
+    k = torch.randn((1, H, T, d), device=DEV, generator=g)
+    v = torch.zeros_like(k)
+    v[:, :, ::16] = torch.randn((1, H, 8, d), device=DEV, generator=g)  # lane group 0's keys
+    c = torch.zeros((1, H, T), device=DEV)
+    c[..., :64] = 0.4375
+    o, _ = fox.fox_attn_decode(torch.zeros((1, H, d), device=DEV), k, v, c,
+                               torch.full((1, H), 100.0, device=DEV))
+    x = torch.tensor(0.4375) * torch.tensor(1.4426950408889634)  # the score, as the kernel has it
+    vs, f32 = v[0, :, ::16].cpu(), torch.float32
+    first = ((vs[:, 0] + vs[:, 1]) + vs[:, 2]) + vs[:, 3]
+    mismatches = []
+    for ulp in range(-2, 3):
+        alpha = torch.exp2(-x.double()).to(f32)
+        alpha = (alpha.view(torch.int32) + ulp).view(f32)
+        acc = (alpha.double() * first.double() + vs[:, 4].double()).to(f32)
+        for u in (5, 6, 7):
+            acc = acc + vs[:, u]
+        l = (alpha.double() * 4 + 1).to(f32) + 1 + 1 + 1
+        total = torch.zeros((), dtype=f32)
+        for _ in range(16):  # the lane groups' equal sums
+            total = total + l
+        mismatches.append(int((acc / total != o[0].cpu()).sum()))
+    assert min(mismatches) == 0, mismatches
