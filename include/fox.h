@@ -216,10 +216,11 @@ fox_status_t fox_dlogf_from_dc(const float* dc_q, const float* dc_k, float* d_lo
 fox_status_t fox_dlogit_from_dc(const float* dc_q, const float* dc_k, const float* gate_logit,
                        float* d_log_f, float* d_logit, int B, int H, int L, hipStream_t stream);
 
-/* Bytes of workspace for fox_attn_decode at this shape (0 on invalid arguments).  A
- * smaller one that holds the partials of 256-key splits, B*H*ceil(T/256)*(d+2)*4 bytes
- * (a workspace sized for another T, say), is taken too; the keys are then split more
- * coarsely, which changes the order of the sums and, with few heads, costs time. */
+/* Bytes of workspace for fox_attn_decode at this shape and at every shorter T of it (0 on
+ * invalid arguments): a workspace sized for the longest cache serves each step of a
+ * growing one.  A smaller one that holds the partials of 256-key splits,
+ * B*H*ceil(T/256)*(d+2)*4 bytes, is taken too; the keys are then split more coarsely,
+ * which changes the order of the sums and, with few heads, costs time. */
 size_t fox_attn_decode_workspace_bytes(fox_dtype_t dtype, int B, int H, int T, int d);
 
 /*

@@ -57,14 +57,17 @@ static bool decode_direct(int BH, int T, int d, size_t elem) {
 // T = 2000 27.1 / 30.1 and B H = 12, T = 20000, d = 64 18.3 / 20.4.
 //
 // A workspace that holds the partials of 256-key splits always serves: where it is too
-// small for the finer ones (sized for another length, say) the split is the finest that
-// fits.  The size a caller is told covers every finer split of up to T keys, so a
-// workspace sized for the longest cache gives each step of a growing one its own split.
+// small for the finer ones the split is the finest that fits.  The size a caller is told
+// covers the splits of every cache of up to T keys, so a workspace sized for the longest
+// gives each step of a growing one its own split.  (A shorter cache can need more than a
+// longer one: B H = 16 takes 254 splits at T = 65024 and 128 at 65536, where the split
+// doubles.)
 constexpr int kSplitKeys = 256, kFineGroups = 768, kFineSplits = 256, kFineKeys = 32;
+constexpr int kCoarseGroups = 2048;
 
 static int coarse_keys_per_split(int BH, int T) {
   for (int ks = 1024; ks > kSplitKeys; ks >>= 1)
-    if (BH * (((long long)T + ks - 1) / ks) >= 2048) return ks;
+    if (BH * (((long long)T + ks - 1) / ks) >= kCoarseGroups) return ks;
   return kSplitKeys;
 }
 
@@ -93,7 +96,11 @@ size_t decode_workspace_bytes(bool bf16_, int BH, int T, int d) {
   // a split is halved below kFineGroups workgroups only, which at most doubles them
   const long long fine = std::min({(long long)kFineSplits, 2LL * ((kFineGroups - 1) / BH),
                                    (T + kFineKeys - 1LL) / kFineKeys});
-  return std::max(least, partial_bytes(BH, fine, d));
+  // a shorter cache's split of 256 or 512 keys is one whose double would give fewer than
+  // kCoarseGroups workgroups, which at most doubles them
+  const long long coarse =
+      std::min(2LL * ((kCoarseGroups - 1) / BH), (T + kSplitKeys - 1LL) / kSplitKeys);
+  return std::max(least, partial_bytes(BH, std::max(fine, coarse), d));
 }
 
 template <typename Tt>

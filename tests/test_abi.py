@@ -350,6 +350,19 @@ def test_decode_validation_and_workspace(lib):
                                ctypes.c_float(0.1), None) == 2
 
 
+@pytest.mark.parametrize("bh,longest", [(1, 65536), (12, 65536), (16, 131072), (64, 32768),
+                                        (128, 16384), (256, 8192), (768, 3000), (2048, 2049)])
+def test_decode_workspace_serves_shorter_caches(lib, bh, longest):
+    """The workspace told for T keys is enough for every shorter cache, also across the
+    lengths at which the split doubles and the number of partials falls."""
+    for dtype, d in ((1, 128), (0, 64)):
+        most, at = 0, 0
+        for T in range(1, longest + 1):
+            n = lib.fox_attn_decode_workspace_bytes(dtype, 1, bh, T, d)
+            assert n >= most, f"T = {T}: {n} bytes, T = {at}: {most}"
+            most, at = n, T
+
+
 def test_decode_noalloc_validation(lib):
     """The allocation-free decode checks its arguments like fox_attn_decode and
     refuses, before touching the GPU, shapes whose split partials exceed its

@@ -48,7 +48,8 @@ def test_decode_splits(dtype, d, B, H, T):
 
 
 @pytest.mark.parametrize("B,H,T,Tmax", [(1, 2, 8193, 8193), (1, 3, 500, 9000), (2, 8, 6000, 8192),
-                                        (2, 8, 4097, 4097), (1, 16, 47 * 128, 48 * 128)])
+                                        (2, 8, 4097, 4097), (1, 16, 47 * 128, 48 * 128),
+                                        (8, 16, 7600, 8192)])  # 256 keys a split, and 512
 def test_decode_other_workspaces(B, H, T, Tmax):
     """The workspace of 256-key splits alone (coarser splits: the oracle bars; bytes past
     it untouched), and one sized for a longer cache (the same splits, bit for bit)."""
