@@ -1386,6 +1386,16 @@ __global__ __launch_bounds__(kBiasThreads) void fixed_bias_grad_kernel(
   }
 }
 
+static hipError_t launch_bias_grad(const float* dlf, const float* bias, float* d_bias, int BH,
+                                   int H, int L, hipStream_t s) {
+  // a part of the heads is a launch on advanced pointers; H stays the rows' stride
+  launch_in_parts((unsigned)H, kBiasThreads, [&](unsigned first, unsigned n) {
+    hipLaunchKernelGGL(fixed_bias_grad_kernel, dim3(n), dim3(kBiasThreads), 0, s,
+                       dlf + (size_t)first * (size_t)L, bias + first, d_bias + first, BH / H, H, L);
+  });
+  return hipGetLastError();
+}
+
 size_t bwd_fixed_workspace_bytes(int BH, int L) { return 16 * (size_t)BH * (size_t)L; }
 
 hipError_t launch_bwd_fixed(bool bf16_, const void* q, const void* k, const void* v,
@@ -1397,11 +1407,7 @@ hipError_t launch_bwd_fixed(bool bf16_, const void* q, const void* k, const void
   float* dlf = w + 3 * (size_t)BH * L;
   hipError_t e = launch_bwd_stages(bf16_, q, k, v, gate_fixed(bias, H), o, lse, d_o, dq, dk, dv,
                                    dlf, w, BH, L, d, scale, s, q_norm_max, k_norm_max);
-  if (e == hipSuccess && d_bias) {
-    hipLaunchKernelGGL(fixed_bias_grad_kernel, dim3(H), dim3(kBiasThreads), 0, s, dlf, bias,
-                       d_bias, BH / H, H, L);
-    e = hipGetLastError();
-  }
+  if (e == hipSuccess && d_bias) e = launch_bias_grad(dlf, bias, d_bias, BH, H, L, s);
   return e;
 }
 
@@ -1420,11 +1426,7 @@ hipError_t launch_bwd_fixed_stored(const void* q, const void* k, const void* v,
       q, k, v, gate_fixed(bias, H), o, lse, d_o, dq, dk, dv, dlf, w,
       static_cast<char*>(ws) + align256(bwd_fixed_workspace_bytes(BH, L)), BH, L, d, scale, s,
       q_norm_max, k_norm_max);
-  if (e == hipSuccess && d_bias) {
-    hipLaunchKernelGGL(fixed_bias_grad_kernel, dim3(H), dim3(kBiasThreads), 0, s, dlf, bias,
-                       d_bias, BH / H, H, L);
-    e = hipGetLastError();
-  }
+  if (e == hipSuccess && d_bias) e = launch_bias_grad(dlf, bias, d_bias, BH, H, L, s);
   return e;
 }
 

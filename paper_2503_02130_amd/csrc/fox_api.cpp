@@ -13,7 +13,9 @@
 namespace {
 
 constexpr long long kMaxElems = 1LL << 40;        // per tensor
-constexpr long long kMaxWorkgroups = 1LL << 22;   // 256-thread workgroups per launch
+// Workgroups per launch at 64 rows each; kernels of 1024 threads, or of fewer rows, bring
+// more threads than a launch takes and are launched in parts or loop.
+constexpr long long kMaxWorkgroups = 1LL << 22;
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 

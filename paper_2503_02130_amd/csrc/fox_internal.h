@@ -6,6 +6,16 @@
 
 namespace fox {
 
+// A launch takes fewer than 2^32 threads.  The entry points accept up to 2^22 workgroups,
+// which 1024 threads each bring just past that: launch(first, count) is called once for
+// all workgroups, or once for each part of them that fits.
+template <typename F>
+inline void launch_in_parts(unsigned groups, unsigned threads, F&& launch) {
+  const unsigned most = 0xFFFFFFFFu / threads;
+  for (unsigned first = 0; first < groups; first += most)
+    launch(first, groups - first < most ? groups - first : most);
+}
+
 // The forget gates as the attention kernels see them: the prefix array c
 // [BH, L] (data-dependent gates) or one bias per head, b [H] (fixed gates,
 // f_t = sigmoid(b)); bh % H selects a row's head.

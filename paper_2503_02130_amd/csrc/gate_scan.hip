@@ -187,6 +187,19 @@ __global__ __launch_bounds__(256) void log_sigmoid_kernel(const float* __restric
   }
 }
 
+// Rows are independent, so a part of them is a launch on advanced pointers (which stay
+// aligned where rows_aligned holds, L being a multiple of 4).
+template <int MODE, bool VEC>
+static void scan_rows(const float* a, const float* b, const float* g, float* aux, float* out,
+                      int rows, int L, hipStream_t s) {
+  launch_in_parts((unsigned)rows, kScanThreads, [&](unsigned first, unsigned n) {
+    const size_t at = (size_t)first * (size_t)L;
+    auto from = [&](auto* p) { return p ? p + at : p; };
+    hipLaunchKernelGGL((scan_rows_kernel<MODE, VEC>), dim3(n), dim3(kScanThreads), 0, s, from(a),
+                       from(b), from(g), from(aux), from(out), L);
+  });
+}
+
 hipError_t launch_gate_prefix(const float* logit, float* log_f, float* c, int rows, int L,
                               hipStream_t s) {
   const bool aligned = rows_aligned(L, {logit, log_f, c});
@@ -194,28 +207,19 @@ hipError_t launch_gate_prefix(const float* logit, float* log_f, float* c, int ro
     const size_t n4 = (size_t)rows * (size_t)L / 4;
     const unsigned blocks = (unsigned)std::min<size_t>((n4 + 255) / 256, 4096);
     hipLaunchKernelGGL(log_sigmoid_kernel, dim3(blocks), dim3(256), 0, s, logit, log_f, c, n4);
-    hipLaunchKernelGGL((scan_rows_kernel<3, true>), dim3(rows), dim3(kScanThreads), 0, s, c,
-                       nullptr, nullptr, nullptr, c, L);
+    scan_rows<3, true>(c, nullptr, nullptr, nullptr, c, rows, L, s);
     return hipGetLastError();
   }
   // rows of one segment: one pass per row is faster than two launches
-  if (aligned)
-    hipLaunchKernelGGL((scan_rows_kernel<0, true>), dim3(rows), dim3(kScanThreads), 0, s, logit,
-                       nullptr, nullptr, log_f, c, L);
-  else
-    hipLaunchKernelGGL((scan_rows_kernel<0, false>), dim3(rows), dim3(kScanThreads), 0, s, logit,
-                       nullptr, nullptr, log_f, c, L);
+  if (aligned) scan_rows<0, true>(logit, nullptr, nullptr, log_f, c, rows, L, s);
+  else scan_rows<0, false>(logit, nullptr, nullptr, log_f, c, rows, L, s);
   return hipGetLastError();
 }
 
 hipError_t launch_reverse_scan_sum(const float* a, const float* b, float* out, int rows, int L,
                                    hipStream_t s) {
-  if (rows_aligned(L, {a, b, out}))
-    hipLaunchKernelGGL((scan_rows_kernel<1, true>), dim3(rows), dim3(kScanThreads), 0, s, a, b,
-                       nullptr, nullptr, out, L);
-  else
-    hipLaunchKernelGGL((scan_rows_kernel<1, false>), dim3(rows), dim3(kScanThreads), 0, s, a, b,
-                       nullptr, nullptr, out, L);
+  if (rows_aligned(L, {a, b, out})) scan_rows<1, true>(a, b, nullptr, nullptr, out, rows, L, s);
+  else scan_rows<1, false>(a, b, nullptr, nullptr, out, rows, L, s);
   return hipGetLastError();
 }
 
@@ -223,11 +227,9 @@ hipError_t launch_reverse_scan_gate(const float* a, const float* b, const float*
                                     float* d_log_f, float* d_logit, int rows, int L,
                                     hipStream_t s) {
   if (rows_aligned(L, {a, b, logit, d_log_f, d_logit}))
-    hipLaunchKernelGGL((scan_rows_kernel<2, true>), dim3(rows), dim3(kScanThreads), 0, s, a, b,
-                       logit, d_log_f, d_logit, L);
+    scan_rows<2, true>(a, b, logit, d_log_f, d_logit, rows, L, s);
   else
-    hipLaunchKernelGGL((scan_rows_kernel<2, false>), dim3(rows), dim3(kScanThreads), 0, s, a, b,
-                       logit, d_log_f, d_logit, L);
+    scan_rows<2, false>(a, b, logit, d_log_f, d_logit, rows, L, s);
   return hipGetLastError();
 }
 

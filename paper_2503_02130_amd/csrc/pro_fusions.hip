@@ -110,9 +110,10 @@ __global__ __launch_bounds__(kProFwdThreads) void pro_prologue_kernel(
     const T* __restrict__ qr, const T* __restrict__ kr, const T* __restrict__ vr,
     const float* __restrict__ ka, const float* __restrict__ va, const float* __restrict__ wq,
     const float* __restrict__ wk, float eps, T* __restrict__ q, T* __restrict__ k,
-    T* __restrict__ v, int H, int L, int n_chunk) {
+    T* __restrict__ v, int H, int L, int n_chunk, unsigned first_block) {
   constexpr int VEC = ProVec<T>::N, LPR = D / VEC, RPP = kProFwdThreads / LPR;
-  const int bh = (int)(blockIdx.x / n_chunk), chunk = (int)(blockIdx.x % n_chunk);
+  const unsigned blk = first_block + blockIdx.x;
+  const int bh = (int)(blk / n_chunk), chunk = (int)(blk % n_chunk);
   const int part = threadIdx.x % LPR, slot = threadIdx.x / LPR;
   float wqv[VEC], wkv[VEC];
   load_w<VEC>(wq + (size_t)(bh % H) * D + part * VEC, wqv);
@@ -302,9 +303,10 @@ __global__ __launch_bounds__(THREADS) void pro_prologue_bwd_kernel(
 template <typename T, int D>
 __global__ __launch_bounds__(kProFwdThreads) void out_gate_kernel(
     const T* __restrict__ O, const T* __restrict__ G, const float* __restrict__ wo, float eps,
-    T* __restrict__ Y, int H, int L, int n_chunk) {
+    T* __restrict__ Y, int H, int L, int n_chunk, unsigned first_block) {
   constexpr int VEC = ProVec<T>::N, LPR = D / VEC, RPP = kProFwdThreads / LPR;
-  const int bh = (int)(blockIdx.x / n_chunk), chunk = (int)(blockIdx.x % n_chunk);
+  const unsigned blk = first_block + blockIdx.x;
+  const int bh = (int)(blk / n_chunk), chunk = (int)(blk % n_chunk);
   const int part = threadIdx.x % LPR, slot = threadIdx.x / LPR;
   float w[VEC];
   load_w<VEC>(wo + (size_t)(bh % H) * D + part * VEC, w);
@@ -440,9 +442,11 @@ static void prologue_t(const void* qr, const void* kr, const void* vr, const flo
                        const float* va, const float* wq, const float* wk, float eps, void* q,
                        void* k, void* v, int H, int BH, int L, hipStream_t s) {
   const int nc = pro_chunks(L);
-  hipLaunchKernelGGL((pro_prologue_kernel<T, D>), dim3((unsigned)(BH * nc)),
-                     dim3(kProFwdThreads), 0, s, (const T*)qr, (const T*)kr, (const T*)vr, ka, va,
-                     wq, wk, eps, (T*)q, (T*)k, (T*)v, H, L, nc);
+  launch_in_parts((unsigned)(BH * nc), kProFwdThreads, [&](unsigned first, unsigned n) {
+    hipLaunchKernelGGL((pro_prologue_kernel<T, D>), dim3(n), dim3(kProFwdThreads), 0, s,
+                       (const T*)qr, (const T*)kr, (const T*)vr, ka, va, wq, wk, eps, (T*)q, (T*)k,
+                       (T*)v, H, L, nc, first);
+  });
 }
 
 hipError_t launch_pro_prologue(bool bf16_, const void* qr, const void* kr, const void* vr,
@@ -507,24 +511,24 @@ hipError_t launch_pro_prologue_bwd(bool bf16_, const void* qr, const void* kr, c
   return hipGetLastError();
 }
 
+template <typename T, int D>
+static void out_gate_t(const void* o, const void* g, const float* wo, float eps, void* y, int H,
+                       int BH, int L, hipStream_t s) {
+  const int nc = pro_chunks(L);
+  launch_in_parts((unsigned)(BH * nc), kProFwdThreads, [&](unsigned first, unsigned n) {
+    hipLaunchKernelGGL((out_gate_kernel<T, D>), dim3(n), dim3(kProFwdThreads), 0, s, (const T*)o,
+                       (const T*)g, wo, eps, (T*)y, H, L, nc, first);
+  });
+}
+
 hipError_t launch_out_gate(bool bf16_, const void* o, const void* g, const float* wo, float eps,
                            void* y, int H, int BH, int L, int d, hipStream_t s) {
-  const int nc = pro_chunks(L);
-  const dim3 grid((unsigned)(BH * nc)), block(kProFwdThreads);
   if (bf16_) {
-    if (d == 128)
-      hipLaunchKernelGGL((out_gate_kernel<bf16, 128>), grid, block, 0, s, (const bf16*)o,
-                         (const bf16*)g, wo, eps, (bf16*)y, H, L, nc);
-    else
-      hipLaunchKernelGGL((out_gate_kernel<bf16, 64>), grid, block, 0, s, (const bf16*)o,
-                         (const bf16*)g, wo, eps, (bf16*)y, H, L, nc);
+    if (d == 128) out_gate_t<bf16, 128>(o, g, wo, eps, y, H, BH, L, s);
+    else out_gate_t<bf16, 64>(o, g, wo, eps, y, H, BH, L, s);
   } else {
-    if (d == 128)
-      hipLaunchKernelGGL((out_gate_kernel<float, 128>), grid, block, 0, s, (const float*)o,
-                         (const float*)g, wo, eps, (float*)y, H, L, nc);
-    else
-      hipLaunchKernelGGL((out_gate_kernel<float, 64>), grid, block, 0, s, (const float*)o,
-                         (const float*)g, wo, eps, (float*)y, H, L, nc);
+    if (d == 128) out_gate_t<float, 128>(o, g, wo, eps, y, H, BH, L, s);
+    else out_gate_t<float, 64>(o, g, wo, eps, y, H, BH, L, s);
   }
   return hipGetLastError();
 }

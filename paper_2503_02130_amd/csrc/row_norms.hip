@@ -80,13 +80,12 @@ static void row_norm_t(const void* x, float* out, int BH, int L, int d, hipStrea
   const long long full = (long long)BH * ((L + kNormChunk - 1) / kNormChunk);
   const int rows = full >= 128 ? kNormChunk : kNormChunk / 2;
   const int n_chunk = (L + rows - 1) / rows;
-  const dim3 grid((unsigned)BH * (unsigned)n_chunk);
-  if (d == 128)
-    hipLaunchKernelGGL((row_norm_max_kernel<Tt, 128>), grid, dim3(kNormThreads), 0, s,
-                       (const Tt*)x, out, L, n_chunk, rows);
-  else
-    hipLaunchKernelGGL((row_norm_max_kernel<Tt, 64>), grid, dim3(kNormThreads), 0, s,
-                       (const Tt*)x, out, L, n_chunk, rows);
+  auto kern = d == 128 ? row_norm_max_kernel<Tt, 128> : row_norm_max_kernel<Tt, 64>;
+  // a part holds whole heads: the pointers advance
+  launch_in_parts((unsigned)BH, (unsigned)(n_chunk * kNormThreads), [&](unsigned first, unsigned n) {
+    hipLaunchKernelGGL(kern, dim3(n * (unsigned)n_chunk), dim3(kNormThreads), 0, s,
+                       (const Tt*)x + (size_t)first * (size_t)L * d, out + first, L, n_chunk, rows);
+  });
 }
 
 hipError_t launch_row_norm_max(bool bf16_, const void* x, float* out, int BH, int L, int d,
