@@ -46,3 +46,49 @@ def test_f32_forward_backward(B, H, L, d, fixed):
     check_fwd("f32", o, lse, O, LSE, f"L={L}")
     for name, a, r in zip(("dQ", "dK", "dV", "dlogf"), got, ref):
         check_grad("f32", name, a, r, f"L={L}")
+
+
+@pytest.mark.parametrize("fixed", [False, True])
+def test_f32_more_row_blocks_than_workgroups(fixed):
+    """Past 2^22 row blocks a workgroup walks several, in the same LDS: B H = 2^21 + 8 rows
+    of two blocks, whose last 16 blocks are second ones of their workgroups (two of its
+    four waves have no tile there and run ahead of the others).  Rows are independent and
+    both calls split the tiles alike, so the rows these blocks belong to must have the bits
+    of a call on them alone."""
+    BH, L, d = (1 << 21) + 8, 33, 64
+    if torch.cuda.mem_get_info()[0] < 100 << 30:
+        pytest.skip("needs 100 GB of free GPU memory")
+    gen = torch.Generator("cuda:0").manual_seed(1)
+
+    def rand(*shape):
+        return torch.randn(shape, device="cuda:0", generator=gen)
+
+    x, logit, delta, bias = rand(1, BH, L, d), rand(1, BH, L), rand(1, BH, L), rand(BH)
+    tail = slice(BH - 32, BH)
+    part = tuple(t[:, tail].clone() for t in (x, logit, delta)) + (bias[tail].clone(),)
+
+    def run(x, logit, delta, bias):
+        """The results' last 32 rows; each large one is dropped before the next is made."""
+        s, out = fox.default_scale(d), []
+
+        def keep(r):
+            out.extend(t[:, -32:].clone() for t in r)
+
+        if fixed:
+            o, lse = fox.fox_attn_fwd_fixed_gate(x, x, x, bias, s)
+            keep((o, lse))
+            keep(fox.fox_attn_bwd_fixed_gate(x, x, x, bias, o, lse, x, s)[:3])
+            return out
+        c = fox.fox_gate_prefix(logit)
+        o, lse = fox.fox_attn_fwd(x, x, x, c, s)
+        keep((o, lse))
+        del o
+        keep(fox.fox_attn_bwd_dkdv(x, x, x, c, lse, x, delta, s))
+        keep(fox.fox_attn_bwd_dq(x, x, x, c, lse, x, delta, s))
+        return out
+
+    whole = run(x, logit, delta, bias)
+    del x, logit, delta
+    torch.cuda.empty_cache()
+    for i, (w, one) in enumerate(zip(whole, run(*part))):
+        assert bool(torch.isfinite(one).all()) and torch.equal(w, one), f"output {i}"
