@@ -265,8 +265,8 @@ __global__ __launch_bounds__(kDecThreads) void decode_split_kernel(
     }
   }
 
-  decode_keys<Tt, D, FIXED, kDecThreads>(kh, vh, gate + head, T, cT, lf, kbeg, kend, g, qv, m, l,
-                                         acc);
+  decode_keys<Tt, D, FIXED, kDecThreads>(kh, vh, FIXED ? gate : gate + head, T, cT, lf, kbeg, kend,
+                                         g, qv, m, l, acc);
 
 #pragma unroll
   for (int e = 0; e < VEC; ++e) s_acc[g][lp * VEC + e] = acc[e];

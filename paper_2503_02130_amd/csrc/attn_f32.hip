@@ -436,7 +436,6 @@ void bwd_dkdv_f32_kernel(const float* __restrict__ Q, const float* __restrict__ 
                          float* __restrict__ dV, float* __restrict__ dck, int BH, int H, int L,
                          int n_blk, float scale, float scale_log2) {
   constexpr int NL = f32_tile_loads<D>();
-  constexpr int NR = FIXED ? 2 : 3;  // row-statistics loads
   __shared__ F32KvSmem<D, NW> sm;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
