@@ -16,37 +16,40 @@ namespace fox {
 
 // A workgroup takes kNormChunk rows, half as many where that leaves CUs idle; its passes
 // are a chain of waits for memory, so it is as large as it gets (one or two passes).
-// Smaller chunks for more workgroups do not pay: the chunk maxima of neighbouring heads
-// meet in one cache line, whose atomics run one after the other (1024 of them took
-// 17 us at B H = 16, L = 8192, more than reading the 33.5 MB).  Measured there 15.7 ->
-// 8.8 us against 256 threads per 1024 rows; with 512 rows 8.9 us there, 28 against 24 at
-// B H = 32, L = 16384, but 6.3 against 7.3 at B H = 2, L = 16384 (32 workgroups).
+// Smaller chunks for more workgroups do not pay: the chunk maxima of a head, and of its
+// neighbours, meet in one cache line, whose atomics run one after the other (1024 of them
+// took 17 us at B H = 16, L = 8192, more than reading the 33.5 MB).  Measured there, bf16
+// at d = 128, 15.7 -> 8.8 us against 256 threads per 1024 rows; with 512 rows 8.9 us there,
+// 28 against 24 at B H = 32, L = 16384, but 6.3 against 7.3 at B H = 2, L = 16384 (32
+// workgroups).  bf16 at d = 64 loads 512 rows with four loads a lane group, not eight:
+// B H = 2, L = 16384 5.3 -> 4.5 us, B H = 12, L = 2048 5.1 -> 4.3 (1024 rows 4.9 both).
 constexpr int kNormThreads = 1024;
 constexpr int kNormChunk = 1024;
-constexpr int kNormAhead = 8;     // rows per lane group whose loads are in flight together
+constexpr int kNormAhead = 8;
 
 __global__ void zero_kernel(float* __restrict__ out, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) out[i] = 0.0f;
 }
 
-template <typename Tt, int D>
+template <typename Tt, int D, int ROWS>
 __global__ __launch_bounds__(kNormThreads) void row_norm_max_kernel(const Tt* __restrict__ x,
                                                                     float* __restrict__ out,
-                                                                    int L, int n_chunk,
-                                                                    int chunk_rows) {
+                                                                    int L, int n_chunk) {
   constexpr int VEC = 16 / (int)sizeof(Tt);
   constexpr int LPR = D / VEC;                 // lanes per row
-  constexpr int RPI = kNormThreads / LPR;      // rows per pass
+  constexpr int RPI = kNormThreads / LPR;      // rows per load
+  // rows per lane group whose loads are in flight together, no more than the chunk has
+  constexpr int AHEAD = ROWS / RPI < kNormAhead ? ROWS / RPI : kNormAhead;
   const int bh = blockIdx.x / n_chunk, chunk = blockIdx.x % n_chunk;
   const int tid = threadIdx.x, g = tid / LPR, lp = tid % LPR;
-  const int r0 = chunk * chunk_rows, r1 = min(L, r0 + chunk_rows);
+  const int r0 = chunk * ROWS, r1 = min(L, r0 + ROWS);
   const Tt* base = x + (size_t)bh * (size_t)L * D + lp * VEC;
   float best = 0.0f;
-  for (int rb = r0 + g; rb < r1; rb += kNormAhead * RPI) {
-    float ss[kNormAhead];
+  for (int rb = r0 + g; rb < r1; rb += AHEAD * RPI) {
+    float ss[AHEAD];
 #pragma unroll
-    for (int u = 0; u < kNormAhead; ++u) {
+    for (int u = 0; u < AHEAD; ++u) {
       const int r = min(rb + u * RPI, r1 - 1);  // rows past the chunk repeat its last row
       ss[u] = 0.0f;
       if constexpr (sizeof(Tt) == 2) {
@@ -60,7 +63,7 @@ __global__ __launch_bounds__(kNormThreads) void row_norm_max_kernel(const Tt* __
       }
     }
 #pragma unroll
-    for (int u = 0; u < kNormAhead; ++u) best = fmaxf(best, row_sum<LPR>(ss[u]));
+    for (int u = 0; u < AHEAD; ++u) best = fmaxf(best, row_sum<LPR>(ss[u]));
   }
   __shared__ float s_best[kNormThreads / 64];
 #pragma unroll
@@ -75,17 +78,22 @@ __global__ __launch_bounds__(kNormThreads) void row_norm_max_kernel(const Tt* __
   }
 }
 
-template <typename Tt>
-static void row_norm_t(const void* x, float* out, int BH, int L, int d, hipStream_t s) {
-  const long long full = (long long)BH * ((L + kNormChunk - 1) / kNormChunk);
-  const int rows = full >= 128 ? kNormChunk : kNormChunk / 2;
-  const int n_chunk = (L + rows - 1) / rows;
-  auto kern = d == 128 ? row_norm_max_kernel<Tt, 128> : row_norm_max_kernel<Tt, 64>;
+template <typename Tt, int ROWS>
+static void row_norm_rows(const void* x, float* out, int BH, int L, int d, hipStream_t s) {
+  const int n_chunk = (L + ROWS - 1) / ROWS;
+  auto kern = d == 128 ? row_norm_max_kernel<Tt, 128, ROWS> : row_norm_max_kernel<Tt, 64, ROWS>;
   // a part holds whole heads: the pointers advance
   launch_in_parts((unsigned)BH, (unsigned)(n_chunk * kNormThreads), [&](unsigned first, unsigned n) {
     hipLaunchKernelGGL(kern, dim3(n * (unsigned)n_chunk), dim3(kNormThreads), 0, s,
-                       (const Tt*)x + (size_t)first * (size_t)L * d, out + first, L, n_chunk, rows);
+                       (const Tt*)x + (size_t)first * (size_t)L * d, out + first, L, n_chunk);
   });
+}
+
+template <typename Tt>
+static void row_norm_t(const void* x, float* out, int BH, int L, int d, hipStream_t s) {
+  const long long full = (long long)BH * ((L + kNormChunk - 1) / kNormChunk);
+  if (full >= 128) row_norm_rows<Tt, kNormChunk>(x, out, BH, L, d, s);
+  else row_norm_rows<Tt, kNormChunk / 2>(x, out, BH, L, d, s);
 }
 
 hipError_t launch_row_norm_max(bool bf16_, const void* x, float* out, int BH, int L, int d,
