@@ -157,8 +157,11 @@ __device__ __forceinline__ void fwd_bf16_body(
   const int kend = min(L, q0 + kFwdBM);
   const int t_last = (kend + kFwdBN - 1) / kFwdBN - 1;
   const int t_diag = qw0 / kFwdBN;  // tile holding this wave's diagonal
-  // skip test in the units of the stored key terms ((c_q0 - c_j) / s)
-  const float skip_norm = SKIP ? 2.0f * qnorm[bh] * knorm[bh] : 0.0f;
+  // Skip test in the units of the stored key terms ((c_q0 - c_j) / s).  All it compares is
+  // in LDS, loaded by one wave, so that the waves of a group leave the tile loop together
+  // whatever happens to the norms in memory meanwhile: one that stayed would wait for ever.
+  __shared__ float skip_norm;
+  if (SKIP && tid == 0) skip_norm = 2.0f * qnorm[bh] * knorm[bh];
 
   // wave 0 stages the key terms of the next tile: the prefix values are loaded
   // with the tile's DMA and converted after the tile body, so that waiting for

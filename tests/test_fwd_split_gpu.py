@@ -46,3 +46,24 @@ def test_split_forward(d, L):
     assert torch.equal(op, o) and torch.equal(lsep, lse)
     # two bf16 roundings of one fp32 value formed in different orders
     assert rel_l2(y, fox.fox_pro_output_gate(o, x["do"], wo)) <= 1e-3
+
+
+@pytest.mark.parametrize("d,B,H,L", [(128, 1, 16, 3001), (64, 1, 16, 3001)])
+def test_split_skipping_ends_whatever_the_norms_do(d, B, H, L):
+    """The norms change in memory while the skipping forward runs: what it then computes is
+    nobody's business, but every wave group must leave its tile loop as one (a wave that
+    stayed alone would wait for ever), and the next call is right again."""
+    x = inputs.attn_inputs(B, H, L, d, "bf16", ("normal", 2.0, 1.0), L, device=DEV)
+    q, k, v = x["q"], x["k"], x["v"]
+    c = fox.fox_gate_prefix(x["logit"])
+    qn, kn = fox.fox_row_norm_max(q), fox.fox_row_norm_max(k)
+    moving, other = kn.clone(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for i in range(20):
+        with torch.cuda.stream(other):
+            for j in range(20):
+                moving.fill_(100.0 * (j % 2))
+        fox.fox_attn_fwd_skip(q, k, v, c, qn, moving)
+    torch.cuda.synchronize()
+    for a, b in zip(fox.fox_attn_fwd_skip(q, k, v, c, qn, kn), fox.fox_attn_fwd(q, k, v, c)):
+        assert torch.equal(a, b)
