@@ -56,6 +56,13 @@ static bool decode_direct(int BH, int T, int d, size_t elem) {
 // 9.0 / 8.0; B H = 2, T = 32768 21.6 / 19.6 / 25.2 / 41.9; above the line, B H = 128,
 // T = 2000 27.1 / 30.1 and B H = 12, T = 20000, d = 64 18.3 / 20.4.
 //
+// A split below one pass of the workgroup's loads (16 KB of keys) leaves some of them
+// unused.  That still pays for few heads with prefix gates (above), but not with fixed gates
+// (us, 32 keys / one pass: bf16, d = 64, B H = 16, T = 3000 10.1 / 7.1, B H = 64, T = 600
+// 8.9 / 7.2, fp32, d = 64, B H = 64, T = 600 8.1 / 7.2; the two are one at fp32, d = 128) nor
+// with more heads than the one-launch form takes, whose caches may be as short as a pass
+// (bf16, d = 64, B H = 320, T = 100 9.8 / 8.6).
+//
 // A workspace that holds the partials of 256-key splits always serves: where it is too
 // small for the finer ones the split is the finest that fits.  The size a caller is told
 // covers the splits of every cache of up to T keys, so a workspace sized for the longest
@@ -75,11 +82,13 @@ static size_t partial_bytes(int BH, long long splits, int d) {
   return (size_t)BH * (size_t)splits * (size_t)(d + 2) * sizeof(float);
 }
 
-static int decode_keys_per_split(int BH, int T, int d, size_t ws_bytes) {
+static int decode_keys_per_split(int BH, int T, int d, size_t elem, bool fixed, size_t ws_bytes) {
+  const int pass = (int)((size_t)kDecThreads * kDecUnroll * 16 / (d * elem));
+  const int least = fixed || BH > kDirectGroups ? std::max(pass, kFineKeys) : kFineKeys;
   auto splits = [&](int ks) { return ((long long)T + ks - 1) / ks; };
   int ks = coarse_keys_per_split(BH, T);
   if (ks == kSplitKeys)
-    while (ks > kFineKeys && BH * splits(ks) < kFineGroups && splits(ks / 2) <= kFineSplits &&
+    while (ks > least && BH * splits(ks) < kFineGroups && splits(ks / 2) <= kFineSplits &&
            partial_bytes(BH, splits(ks / 2), d) <= ws_bytes)
       ks >>= 1;
   return ks;
@@ -367,43 +376,52 @@ __global__ __launch_bounds__(kDirectThreads) void decode_direct_kernel(
   }
 }
 
-// The splits' partials of one (batch, head): kCombineThreads / D thread groups take
-// every kCombineThreads / D-th split each (all of a thread's loads independent), the
+// The splits' partials of one (batch, head): THREADS / D thread groups take
+// every THREADS / D-th split each (all of a thread's loads independent), the
 // maximum is found by each wave over the splits in parallel, and the groups meet in LDS.
 // One thread per element walking every split twice took most of a long, narrow step:
-// B H = 2, T = 32768 72 -> 22 us for the step at the same split.
+// B H = 2, T = 32768 72 -> 22 us for the step at the same split.  A single split needs one
+// thread per element and no search (THREADS = D; many heads, bf16, d = 64, B H = 512,
+// T = 30 8.0 -> 7.5 us for the step).
 constexpr int kCombineThreads = 512;
-template <typename Tt, int D>
-__global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(
+template <typename Tt, int D, int THREADS>
+__global__ __launch_bounds__(THREADS) void decode_combine_kernel(
     const float* __restrict__ part, float* __restrict__ cc, const float* __restrict__ x_new,
     Tt* __restrict__ o, float* __restrict__ lse, int T, int n_split) {
-  constexpr int NG = kCombineThreads / D;
-  __shared__ float s_acc[NG][D];
-  __shared__ float s_l[NG];
+  constexpr int NG = THREADS / D;
   const int bh = blockIdx.x, tid = threadIdx.x;
   const int g = tid / D, e = tid % D;
   const float* p = part + (size_t)bh * n_split * (D + 2);
-  float M = -INFINITY;
-  for (int s = tid & 63; s < n_split; s += 64) M = fmaxf(M, p[(size_t)s * (D + 2)]);
+  float M, Ls, acc;
+  if constexpr (NG == 1) {  // n_split == 1
+    M = p[0];
+    Ls = p[1];
+    acc = p[2 + e];
+  } else {
+    __shared__ float s_acc[NG][D];
+    __shared__ float s_l[NG];
+    M = -INFINITY;
+    for (int s = tid & 63; s < n_split; s += 64) M = fmaxf(M, p[(size_t)s * (D + 2)]);
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
-  float Ls = 0.0f, acc = 0.0f;
+    for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
+    Ls = acc = 0.0f;
 #pragma unroll 4
-  for (int s = g; s < n_split; s += NG) {
-    const float* ps = p + (size_t)s * (D + 2);
-    const float w = exp2_fast(ps[0] - M);
-    Ls += ps[1] * w;
-    acc += ps[2 + e] * w;
-  }
-  s_acc[g][e] = acc;
-  if (e == 0) s_l[g] = Ls;
-  __syncthreads();
-  if (g > 0) return;
-  Ls = s_l[0];
+    for (int s = g; s < n_split; s += NG) {
+      const float* ps = p + (size_t)s * (D + 2);
+      const float w = exp2_fast(ps[0] - M);
+      Ls += ps[1] * w;
+      acc += ps[2 + e] * w;
+    }
+    s_acc[g][e] = acc;
+    if (e == 0) s_l[g] = Ls;
+    __syncthreads();
+    if (g > 0) return;
+    Ls = s_l[0];
 #pragma unroll
-  for (int k = 1; k < NG; ++k) {
-    acc += s_acc[k][e];
-    Ls += s_l[k];
+    for (int k = 1; k < NG; ++k) {
+      acc += s_acc[k][e];
+      Ls += s_l[k];
+    }
   }
   o[(size_t)bh * D + e] = (Tt)(acc / Ls);
   if (tid == 0) {
@@ -427,7 +445,7 @@ static hipError_t launch_decode_t(const void* q, const void* k_cache, const void
                        scale * kLog2e);
     return hipGetLastError();
   }
-  const int ks = decode_keys_per_split(BH, T, D, ws_bytes);
+  const int ks = decode_keys_per_split(BH, T, D, sizeof(Tt), FIXED, ws_bytes);
   const int n_split = (T + ks - 1) / ks;
   float* part = static_cast<float*>(ws);
   hipLaunchKernelGGL((decode_split_kernel<Tt, D, FIXED, SKIP>),
@@ -436,7 +454,9 @@ static hipError_t launch_decode_t(const void* q, const void* k_cache, const void
                      part, H, T, ks, n_split, scale * kLog2e);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((decode_combine_kernel<Tt, D>), dim3(BH), dim3(kCombineThreads), 0, s, part, c_cache,
+  const bool one = n_split == 1;
+  auto combine = one ? decode_combine_kernel<Tt, D, D> : decode_combine_kernel<Tt, D, kCombineThreads>;
+  hipLaunchKernelGGL(combine, dim3(BH), dim3(one ? D : kCombineThreads), 0, s, part, c_cache,
                      logit_new, (Tt*)o, lse, T, n_split);
   return hipGetLastError();
 }

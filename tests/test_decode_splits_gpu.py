@@ -22,7 +22,9 @@ CASES = ([("bf16", 128, 1, 3, T) for T in (2, 31, 32, 33, 500, 8192, 8193)] +
          # direct and, one key or head more, split
          [("bf16", 128, 1, 2, 256), ("bf16", 128, 1, 2, 257), ("bf16", 64, 1, 2, 512),
           ("bf16", 64, 1, 2, 513), ("f32", 128, 1, 2, 128), ("f32", 128, 1, 2, 129),
-          ("f32", 64, 2, 2, 255), ("bf16", 128, 16, 16, 40), ("bf16", 128, 257, 1, 40)])
+          ("f32", 64, 2, 2, 255), ("bf16", 128, 16, 16, 40), ("bf16", 128, 257, 1, 40),
+         # many heads: one pass of a workgroup's loads is one split, a key more two
+         ("bf16", 64, 257, 1, 128), ("bf16", 64, 257, 1, 129), ("f32", 128, 129, 2, 65)])
 
 
 @pytest.mark.parametrize("dtype,d,B,H,T", CASES)
@@ -74,6 +76,26 @@ def test_decode_other_workspaces(B, H, T, Tmax):
     O, LSE, cT = oracle.decode(xc["q"], xc["k_cache"], xc["v_cache"], xc["cached_logit"],
                                xc["logit_new"], fox.default_scale(d))
     check_fwd("bf16", os_, lses, O, LSE, f"T={T}", c_abs=float(cT.abs().max()), L=T)
+
+
+@pytest.mark.parametrize("dtype,d,B,H,T", [("bf16", 64, 2, 3, 513), ("bf16", 64, 1, 2, 769),
+                                           ("bf16", 128, 1, 3, 321), ("f32", 64, 1, 2, 257),
+                                           ("f32", 128, 1, 2, 129), ("bf16", 64, 257, 1, 129)])
+def test_fixed_gate_decode_splits(dtype, d, B, H, T):
+    """Fixed gates, whose splits keep one pass of a workgroup's loads: last splits of one
+    key, against the oracle with the bias as every token's logit; skipping bit for bit."""
+    x = inputs.decode_inputs(B, H, T, d, dtype, ("normal", 3.0, 1.0), T + d, device=DEV)
+    b = fox.fox_fixed_gate_init(H, 2.0, 400.0) if H > 1 else torch.tensor([3.0])
+    args, g = (x["q"], x["k_cache"], x["v_cache"]), b.to(DEV)
+    o, lse = fox.fox_attn_decode_fixed_gate(*args, g)
+    kn = fox.fox_row_norm_max(x["k_cache"])
+    os_, lses = fox.fox_attn_decode_fixed_gate_skip(*args, g, kn)
+    assert torch.equal(os_, o) and torch.equal(lses, lse)
+    xc = cpu(x)
+    O, LSE, cT = oracle.decode(xc["q"], xc["k_cache"], xc["v_cache"],
+                               b[None, :, None].expand(B, H, T - 1), b[None].expand(B, H),
+                               fox.default_scale(d))
+    check_fwd(dtype, o, lse, O, LSE, f"T={T}", c_abs=float(cT.abs().max()), L=T)
 
 
 def test_decode_rounding():
