@@ -25,7 +25,14 @@ namespace fox {
 // hold a row's operands in registers and reduce weight gradients at the end: 512 threads
 // where every workgroup has a CU (B H = 48, L = 163, fp32 34 -> 23.5 us for the prologue's),
 // 256 with more workgroups (B H = 32, L = 4096 53 us against 57 with 512).
-constexpr int kProFwdThreads = 1024;
+// On full grids (kProFullGroups workgroups) of short slices, whose rows leave most of 1024
+// threads idle, 256 do better (us, 1024 / 256 threads: prologue, bf16, d = 64, B H = 768,
+// L = 40 6.1 / 5.3, L = 100 11.7 / 11.0; output gate, bf16, B H = 1024, L = 40 5.8 / 5.0 at
+// d = 64, B H = 2048 15.0 / 13.9 at d = 128; but B H = 768, L = 100 8.1 / 8.7).  The output
+// gate's bf16 rows of 64, a third of the prologue's bytes, also do where 256 threads fill the
+// part (B H = 512, L = 600 25.5 / 23.7, B H = 4096, L = 300 135 / 123; 1152 workgroups, B H =
+// 384, L = 600 20.6 / 21.6).
+constexpr int kProFwdThreads = 1024, kProFwdFew = 256, kProFullGroups = 768;
 constexpr int kProBwdThreads = 256, kProBwdWide = 512, kProWideGroups = 256;
 constexpr int kProRows = 256;  // rows of one (batch, head) slice per workgroup
 
@@ -105,13 +112,13 @@ __device__ __forceinline__ void store_weight_partial(float (*red)[D], const floa
 // ---------------------------------------------------------------------------
 // prologue, forward
 // ---------------------------------------------------------------------------
-template <typename T, int D>
-__global__ __launch_bounds__(kProFwdThreads) void pro_prologue_kernel(
+template <typename T, int D, int THREADS>
+__global__ __launch_bounds__(THREADS) void pro_prologue_kernel(
     const T* __restrict__ qr, const T* __restrict__ kr, const T* __restrict__ vr,
     const float* __restrict__ ka, const float* __restrict__ va, const float* __restrict__ wq,
     const float* __restrict__ wk, float eps, T* __restrict__ q, T* __restrict__ k,
     T* __restrict__ v, int H, int L, int n_chunk, unsigned first_block) {
-  constexpr int VEC = ProVec<T>::N, LPR = D / VEC, RPP = kProFwdThreads / LPR;
+  constexpr int VEC = ProVec<T>::N, LPR = D / VEC, RPP = THREADS / LPR;
   const unsigned blk = first_block + blockIdx.x;
   const int bh = (int)(blk / n_chunk), chunk = (int)(blk % n_chunk);
   const int part = threadIdx.x % LPR, slot = threadIdx.x / LPR;
@@ -300,11 +307,11 @@ __global__ __launch_bounds__(THREADS) void pro_prologue_bwd_kernel(
 // output norm and gate, forward (the bf16 attention forward applies it in its
 // epilogue; this kernel serves the fp32 path and standalone use)
 // ---------------------------------------------------------------------------
-template <typename T, int D>
-__global__ __launch_bounds__(kProFwdThreads) void out_gate_kernel(
+template <typename T, int D, int THREADS>
+__global__ __launch_bounds__(THREADS) void out_gate_kernel(
     const T* __restrict__ O, const T* __restrict__ G, const float* __restrict__ wo, float eps,
     T* __restrict__ Y, int H, int L, int n_chunk, unsigned first_block) {
-  constexpr int VEC = ProVec<T>::N, LPR = D / VEC, RPP = kProFwdThreads / LPR;
+  constexpr int VEC = ProVec<T>::N, LPR = D / VEC, RPP = THREADS / LPR;
   const unsigned blk = first_block + blockIdx.x;
   const int bh = (int)(blk / n_chunk), chunk = (int)(blk % n_chunk);
   const int part = threadIdx.x % LPR, slot = threadIdx.x / LPR;
@@ -437,13 +444,25 @@ size_t bwd_pro_workspace_bytes(bool bf16_, int BH, int L, int d) {
          (size_t)BH * pro_chunks(L) * d * sizeof(float);
 }
 
+// the forward row passes' choice of threads (above)
+template <typename T, int D>
+static bool pro_fwd_few(int groups, int L, bool out_gate) {
+  constexpr int kPass = kProFwdThreads / (D / ProVec<T>::N);  // rows of one pass
+  if (groups < kProFullGroups) return false;
+  if (!out_gate) return L <= kPass;
+  return 8 * L <= 5 * kPass || (D * sizeof(T) == 128 && groups >= 2 * kProFullGroups);
+}
+
 template <typename T, int D>
 static void prologue_t(const void* qr, const void* kr, const void* vr, const float* ka,
                        const float* va, const float* wq, const float* wk, float eps, void* q,
                        void* k, void* v, int H, int BH, int L, hipStream_t s) {
   const int nc = pro_chunks(L);
-  launch_in_parts((unsigned)(BH * nc), kProFwdThreads, [&](unsigned first, unsigned n) {
-    hipLaunchKernelGGL((pro_prologue_kernel<T, D>), dim3(n), dim3(kProFwdThreads), 0, s,
+  const bool few = pro_fwd_few<T, D>(BH * nc, L, false);
+  const int threads = few ? kProFwdFew : kProFwdThreads;
+  auto kern = few ? pro_prologue_kernel<T, D, kProFwdFew> : pro_prologue_kernel<T, D, kProFwdThreads>;
+  launch_in_parts((unsigned)(BH * nc), (unsigned)threads, [&](unsigned first, unsigned n) {
+    hipLaunchKernelGGL(kern, dim3(n), dim3(threads), 0, s,
                        (const T*)qr, (const T*)kr, (const T*)vr, ka, va, wq, wk, eps, (T*)q, (T*)k,
                        (T*)v, H, L, nc, first);
   });
@@ -515,8 +534,11 @@ template <typename T, int D>
 static void out_gate_t(const void* o, const void* g, const float* wo, float eps, void* y, int H,
                        int BH, int L, hipStream_t s) {
   const int nc = pro_chunks(L);
-  launch_in_parts((unsigned)(BH * nc), kProFwdThreads, [&](unsigned first, unsigned n) {
-    hipLaunchKernelGGL((out_gate_kernel<T, D>), dim3(n), dim3(kProFwdThreads), 0, s, (const T*)o,
+  const bool few = pro_fwd_few<T, D>(BH * nc, L, true);
+  const int threads = few ? kProFwdFew : kProFwdThreads;
+  auto kern = few ? out_gate_kernel<T, D, kProFwdFew> : out_gate_kernel<T, D, kProFwdThreads>;
+  launch_in_parts((unsigned)(BH * nc), (unsigned)threads, [&](unsigned first, unsigned n) {
+    hipLaunchKernelGGL(kern, dim3(n), dim3(threads), 0, s, (const T*)o,
                        (const T*)g, wo, eps, (T*)y, H, L, nc, first);
   });
 }

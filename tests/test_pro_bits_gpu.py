@@ -46,6 +46,23 @@ def test_value_shift_rounding(dtype, d):
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("d", [64, 128])
+def test_forward_bits_alone_and_in_a_batch(dtype, d):
+    B, H, L = 100, 16, 20  # 1600 workgroups of 256 threads; 16 of 1024 alone
+    x = inputs.pro_inputs(B, H, L, d, dtype, ("normal", 2.0, 1.0), 5 * d, device=DEV)
+
+    def outs(b):
+        a = [x[n] if n in ("wq", "wk") else x[n][b].clone() for n in NAMES]
+        return fox.fox_pro_prologue(*a, eps=EPS) + (
+            fox.fox_pro_output_gate(a[0], x["g"][b].clone(), x["wo"], eps=EPS),)
+
+    whole = outs(slice(0, B))
+    for b in (0, B - 1):
+        for i, (w, one) in enumerate(zip(whole, outs(slice(b, b + 1)))):
+            assert torch.equal(w[b:b + 1], one), f"row {b} output {i}"
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d", [64, 128])
 def test_backward_bits_alone_and_in_a_batch(dtype, d):
     B, H, L = 20, 8, 300  # 320 workgroups; 16 alone
     x = inputs.pro_inputs(B, H, L, d, dtype, ("normal", 2.0, 1.0), 3 * d, device=DEV)

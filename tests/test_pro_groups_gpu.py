@@ -22,7 +22,10 @@ def _rel(g, r):
 @pytest.mark.parametrize("dtype,d,B,H,L", [
     ("bf16", 128, 1, 2, 33), ("bf16", 64, 1, 3, 255), ("f32", 64, 2, 1, 65),
     ("f32", 128, 16, 16, 31), ("bf16", 64, 16, 16, 129), ("bf16", 128, 16, 8, 257),
-    ("bf16", 128, 1, 257, 3), ("f32", 64, 3, 43, 257), ("f32", 128, 2, 129, 17)])
+    ("bf16", 128, 1, 257, 3), ("f32", 64, 3, 43, 257), ("f32", 128, 2, 129, 17),
+    # 768 workgroups of short slices, 1536 of any (output gate, bf16, d = 64): fewer threads
+    ("bf16", 64, 8, 96, 80), ("bf16", 64, 8, 96, 128), ("f32", 128, 16, 48, 31),
+    ("bf16", 64, 24, 64, 129), ("bf16", 64, 12, 64, 257), ("bf16", 128, 1, 767, 39)])
 def test_pro_launch_shapes(dtype, d, B, H, L):
     x = inputs.pro_inputs(B, H, L, d, dtype, ("normal", 2.0, 1.0), L + d, device="cuda:0")
     args = tuple(x[n] for n in ("q_raw", "k_raw", "v_raw", "k_shift", "v_shift", "wq", "wk"))
