@@ -418,7 +418,8 @@ fox_status_t fox_attn_decode_fixed_gate_skip(fox_dtype_t dtype, const void* q, c
  *   workspace: at least fox_pro_prologue_bwd_workspace_bytes().
  * fox_pro_output_gate: y from an attention output o (standalone epilogue).
  * fox_attn_fwd_pro: fox_attn_fwd followed by the output norm and gate: writes
- *   o and lse (the backward needs them) and y.  bf16 applies the norm and gate
+ *   o and lse (the backward needs them; equal to fox_attn_fwd's to rounding: the
+ *   order of the sums may differ) and y.  bf16 applies the norm and gate
  *   in the attention kernel's epilogue, to o as rounded to bf16; fp32 runs the
  *   standalone epilogue kernel after the attention.
  * fox_attn_bwd_pro: gradients of sum(y o dy): dq, dk, dv, d_log_f as

@@ -559,8 +559,17 @@ void fwd_bf16_split_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ 
 //            512 x 256: 354 / 271            512 x 16: 32.8 / 37.7
 //            640 x 79: 121 / 130             576 x 47: 74.7 / 81.5
 //            1024 x 128: 277 / 287           4096 x 256: 1917 / 2066
-// The rule takes shapes only, so that skipping and dense calls split alike.
-template <int D>
+// With the output norm and gate at D = 128 the merge is followed by the longer epilogue,
+// which one workgroup per CU hides behind nothing, so past one pass of the CUs the rows must
+// be longer (KS = 1 / 2: 384 x 24 44.9 / 48.5, 512 x 32 60.1 / 63.3; 288 x 24 43.3 / 40.7,
+// 384 x 32 alike, 512 x 64 109 / 102).
+// The rule takes shapes only, so that skipping and dense calls split alike and agree bit
+// for bit.  What skipping leaves of a row may be short where the row is not; then the split
+// costs (one workgroup per CU, so two passes of them, each with a merge).  Skipping calls
+// with 257-512 workgroups, before the split / with it: where some heads remember far (gates
+// mixed over heads) 16 heads, L = 3001 68.6 / 56.1 at D = 128, 54.6 / 36.1 at D = 64, where
+// every head forgets within 700 keys 38.3 / 46.6 and 26.6 / 32.6.
+template <int D, bool OUTG>
 static int fwd_groups(int BH, int L) {
   const long long wgs = (long long)BH * ((L + kFwdBM - 1) / kFwdBM);
   const long long tiles = (L + kFwdBN - 1) / kFwdBN;
@@ -568,6 +577,7 @@ static int fwd_groups(int BH, int L) {
     if (wgs <= 512 && tiles >= 24 && 12 * tiles >= wgs) return 4;
     return wgs <= 1024 && tiles >= 12 && 16 * tiles >= wgs ? 2 : 1;
   }
+  if (OUTG && wgs > 256 && 12 * tiles < wgs) return 1;
   return wgs <= 512 && tiles >= 16 && 16 * tiles >= wgs ? 2 : 1;
 }
 
@@ -582,7 +592,7 @@ static void fwd_bf16_t(const void* q, const void* k, const void* v, GateSpec g,
                        (const bf16*)k, (const bf16*)v, g.ptr, qn, kn, (bf16*)o, lse, BH, g.H, L,
                        n_mblk, sl2, og);
   };
-  const int groups = fwd_groups<D>(BH, L);
+  const int groups = fwd_groups<D, OUTG>(BH, L);
   if (groups == 1) launch(fwd_bf16_kernel<D, FIXED, SKIP, OUTG>, 1);
   else if (groups == 2) launch(fwd_bf16_split_kernel<D, FIXED, SKIP, OUTG, 2>, 2);
   else if constexpr (D == 64) launch(fwd_bf16_split_kernel<D, FIXED, SKIP, OUTG, 4>, 4);

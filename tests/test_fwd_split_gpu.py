@@ -67,3 +67,18 @@ def test_split_skipping_ends_whatever_the_norms_do(d, B, H, L):
     torch.cuda.synchronize()
     for a, b in zip(fox.fox_attn_fwd_skip(q, k, v, c, qn, kn), fox.fox_attn_fwd(q, k, v, c)):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("BH,L", [(24, 1500), (32, 1500), (32, 2048)])
+def test_pro_split_line(BH, L):
+    """fox_attn_fwd_pro at d = 128 on both sides of its own line (288 workgroups of up to 24
+    key tiles split; 384 of 24 and 512 of 32 not, where the plain forward splits): o and
+    lse agree with fox_attn_fwd's within two bf16 roundings of sums in different orders."""
+    x = inputs.attn_inputs(1, BH, L, 128, "bf16", ("normal", 3.0, 1.0), L, device=DEV, grad=True)
+    q, k, v, g = x["q"], x["k"], x["v"], x["do"]
+    c = fox.fox_gate_prefix(x["logit"])
+    wo = torch.ones((BH, 128), device=DEV)
+    o, lse = fox.fox_attn_fwd(q, k, v, c)
+    y, op, lsep = fox.fox_attn_fwd_pro(q, k, v, c, g, wo)
+    assert rel_l2(op, o) <= 1e-3 and float((lsep - lse).abs().max()) <= 1e-4
+    assert rel_l2(y, fox.fox_pro_output_gate(op, g, wo)) <= 1e-3
