@@ -1166,20 +1166,20 @@ hipError_t launch_bwd_dkdv(bool bf16_, const void* q, const void* k, const void*
 // Is the grid so short, and the longest row so long, that the row's chain of key tiles
 // decides the time?  Then the tiles are split over the wave groups of one workgroup per
 // CU; where the grid fills the part, several independent workgroups per CU do better.
-// Measured (graph replay, us, one group / split; workgroups x key tiles of the longest
-// row):
-//   D = 64:  64 x 8: 15.4 / 12.9     256 x 16: 25.3 / 20.7   384 x 47: 69.5 / 48.4
-//            480 x 40: 60.5 / 49.4   512 x 256: 351 / 245    512 x 16: 29.8 / 30.8
-//            576 x 24: 44.6 / 48.5   640 x 79: 120 / 120     384 x 5: 11.6 / 17.1
-//   D = 128: 64 x 8: 19.9 / 19.4     256 x 16: 35.1 / 31.5   384 x 47: 97.4 / 77.4
-//            480 x 40: 86.5 / 79.8   512 x 256: 502 / 393    512 x 16: 45.8 / 48.0
-//            576 x 47: 107 / 113     640 x 79: 176 / 178     384 x 5: 18.6 / 24.5
+// Measured (graph replay, us, one group, in its paired order / split; workgroups x key
+// tiles of the longest row):
+//   D = 64:  144 x 24: 35.4 / 25.4   256 x 64: 86.6 / 57.2   384 x 47: 65.2 / 44.7
+//            288 x 11: 19.2 / 18.0   512 x 64: 89.6 / 69.6   512 x 32: 49.1 / 42.3
+//            512 x 16: 29.2 / 29.3   576 x 24: 41.5 / 44.1   640 x 79: 114 / 109
+//   D = 128: 144 x 24: 46.2 / 37.6   256 x 64: 114 / 88.8    384 x 47: 88.7 / 71.0
+//            288 x 11: 27.7 / 26.4   512 x 64: 126 / 110     512 x 32: 70.9 / 65.3
+//            512 x 16: 41.8 / 44.2   576 x 24: 59.1 / 66.4   640 x 79: 171 / 173
+// Below 8 tiles the split loses (384 x 5: 11.6 / 17.1 and 18.6 / 24.5).
 // The rule takes shapes only, so that skipping and dense calls split alike.
 static bool dq_split(unsigned groups, int L) {
   const unsigned tiles = (unsigned)(L + kDqBN - 1) / kDqBN;
   return groups <= 512 && tiles >= 8 && 24 * tiles >= groups;
 }
-
 
 template <int D, bool FIXED>
 static void dq_t(const void* q, const void* k, const void* v, GateSpec g, const float* lse,

@@ -548,27 +548,31 @@ void fwd_bf16_split_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ 
 // not and the longest row's chain of key tiles decides the time.  The split costs a
 // merge (and at D = 128 the second, independent workgroup of a CU), so short rows and
 // full grids keep the unsplit kernel.  Measured (graph replay, us; workgroups x key
-// tiles of the longest row: KS = 1 / 2 / 4):
-//   D = 64:  128 x 16: 17.5 / 16.5 / 16.6    256 x 32: 31.1 / 27.3 / 26.0
-//            384 x 47: 46.3 / 41.1 / 37.0    512 x 32: 36.8 / 35.0 / 36.9
-//            512 x 256: 226 / 193 / 169      640 x 79: 79.9 / 74.8 / 81.6
-//            1024 x 128: 167 / 160 / 176     960 x 19: 33.0 / 35.2 / 50.5
-//            384 x 5: 9.4 / 10.6 / 16.2      4096 x 256: 1054 / 1107 / 1223
-//   D = 128: 256 x 16: 25.5 / 24.7           256 x 32: 43.8 / 38.6
-//            384 x 47: 67.8 / 55.7           512 x 32: 56.3 / 55.2
-//            512 x 256: 354 / 271            512 x 16: 32.8 / 37.7
-//            640 x 79: 121 / 130             576 x 47: 74.7 / 81.5
-//            1024 x 128: 277 / 287           4096 x 256: 1917 / 2066
+// tiles of the longest row: KS = 1, in its paired order / 2 / 4):
+//   D = 64:  144 x 24: 22.8 / 21.1 / 19.8    256 x 32: 30.2 / 26.7 / 24.8
+//            256 x 64: 54.3 / 46.7 / 40.7    384 x 47: 42.4 / 38.2 / 33.7
+//            384 x 24: 25.0 / 23.9 / 24.9    512 x 64: 56.9 / 54.5 / 51.2
+//            512 x 32: 32.8 / 31.9 / 33.9    512 x 16: 20.1 / 20.5 / 25.1
+//            288 x 11: 13.6 / 13.0 / 17.7    576 x 24: 28.3 / 27.9 / 37.8
+//            640 x 79: 73.7 / 71.3 / 79.4    1024 x 128: 148 / 154 / 168
+//   D = 128: 144 x 24: 32.2 / 29.0           256 x 32: 42.6 / 37.5
+//            256 x 64: 78.1 / 64.6           384 x 47: 61.6 / 51.2
+//            384 x 24: 36.3 / 34.0           512 x 64: 87.4 / 79.9
+//            512 x 32: 50.9 / 49.3           512 x 16: 30.4 / 35.0
+//            384 x 16: 27.6 / 29.8           576 x 24: 42.3 / 52.3
+//            640 x 79: 115 / 124             1024 x 128: 253 / 271
+// (At D = 64 the two groups of 513-1024 workgroups serve skipping calls with gates mixed
+// over heads: 1024 x 128 146 / 126, 576 x 47 51.3 / 44.6.)
 // With the output norm and gate at D = 128 the merge is followed by the longer epilogue,
 // which one workgroup per CU hides behind nothing, so past one pass of the CUs the rows must
-// be longer (KS = 1 / 2: 384 x 24 44.9 / 48.5, 512 x 32 60.1 / 63.3; 288 x 24 43.3 / 40.7,
-// 384 x 32 alike, 512 x 64 109 / 102).
+// be longer (KS = 1 / 2: 384 x 24 45.2 / 49.6, 512 x 32 59.7 / 64.9, 504 x 41 67.8 / 74.2;
+// 288 x 24 43.7 / 41.9, 384 x 47 70.5 / 65.0, 512 x 64 95.1 / 94.0).
 // The rule takes shapes only, so that skipping and dense calls split alike and agree bit
 // for bit.  What skipping leaves of a row may be short where the row is not; then the split
 // costs (one workgroup per CU, so two passes of them, each with a merge).  Skipping calls
-// with 257-512 workgroups, before the split / with it: where some heads remember far (gates
-// mixed over heads) 16 heads, L = 3001 68.6 / 56.1 at D = 128, 54.6 / 36.1 at D = 64, where
-// every head forgets within 700 keys 38.3 / 46.6 and 26.6 / 32.6.
+// with 384 x 47, KS = 1 / as split: where some heads remember far (gates mixed over heads)
+// 68.0 / 53.3 at D = 128, 47.4 / 34.2 at D = 64, where every head forgets within 700 keys
+// 36.1 / 46.5 and 24.6 / 32.1.
 template <int D, bool OUTG>
 static int fwd_groups(int BH, int L) {
   const long long wgs = (long long)BH * ((L + kFwdBM - 1) / kFwdBM);
