@@ -157,7 +157,10 @@ def test_forward_gate_regimes(gate, dtype):
 
 # ------------------------------------------- the forward's rescale path
 RESCALE_CASES = [(128, 700, ("constant", 30.0)), (64, 700, ("constant", 30.0)),
-                 (128, 2000, ("normal", 6.0, 1.0)), (64, 300, ("normal", 4.0, 1.0))]
+                 (128, 2000, ("normal", 6.0, 1.0)), (64, 300, ("normal", 4.0, 1.0)),
+                 (64, 800, ("constant", 30.0)), (64, 1600, ("normal", 6.0, 1.0))]
+# the wave groups the kernel splits these short grids' key tiles over (the others: one)
+RESCALE_GROUPS = {(128, 2000): 2, (64, 800): 2, (64, 1600): 4}
 
 
 @pytest.mark.parametrize("d,L,gate", RESCALE_CASES)
@@ -188,7 +191,7 @@ def test_forward_rescale_path(d, L, gate):
     for b in range(B):
         for h in range(H):
             fired, visited, repeat = fwd_rescale_model.rescale_events(
-                xc["q"][b, h], xc["k"][b, h], cc[b, h], s)
+                xc["q"][b, h], xc["k"][b, h], cc[b, h], s, RESCALE_GROUPS.get((d, L), 1))
             print(f"  head {(b, h)}: rescale path on {fired} of {visited} (wave, tile) pairs, "
                   f"up to {repeat} per wave", flush=True)
             assert fired >= max(8, visited // 4) and repeat >= 2, (fired, visited, repeat)
