@@ -28,6 +28,12 @@
  *     a failed validation returns a non-zero fox_status_t and launches nothing.
  *     A failed kernel launch returns FOX_ERR_HIP.  Faults during execution
  *     surface at the caller's next synchronisation.
+ *   - The same call gives the same bits every time.  How the keys (or queries) of a row
+ *     are split over waves depends on the shape, B*H included, so the order of the sums
+ *     does too: a sequence alone and the same sequence in a batch agree to rounding, not
+ *     bit for bit (forward, dQ and all of fp32; decode, where it also depends on the
+ *     workspace).  dK and dV of bf16 and the row-wise Pro kernels' outputs do not depend
+ *     on the batch.
  *   - Causal only (the paper considers causal sequence modelling only, Sec. 2).
  *   - Gate logits must be finite (then log f is finite and c_i - c_j is defined).
  *   - Backward families: every backward (plain, exact skipping, fixed gates, FoX
