@@ -157,11 +157,12 @@ __device__ __forceinline__ void fwd_bf16_body(
   const int kend = min(L, q0 + kFwdBM);
   const int t_last = (kend + kFwdBN - 1) / kFwdBN - 1;
   const int t_diag = qw0 / kFwdBN;  // tile holding this wave's diagonal
-  // Skip test in the units of the stored key terms ((c_q0 - c_j) / s).  All it compares is
-  // in LDS, loaded by one wave, so that the waves of a group leave the tile loop together
-  // whatever happens to the norms in memory meanwhile: one that stayed would wait for ever.
-  __shared__ float skip_norm;
-  if (SKIP && tid == 0) skip_norm = 2.0f * qnorm[bh] * knorm[bh];
+  // Skip test in the units of the stored key terms ((c_q0 - c_j) / s).  One wave loads what
+  // it compares for all, so that the waves of a group leave the tile loop together whatever
+  // happens to the norms in memory meanwhile: one that stayed would wait for ever.
+  __shared__ float norm_bound;
+  float skip_norm = 0.0f;
+  if (SKIP && tid == 0) norm_bound = 2.0f * qnorm[bh] * knorm[bh];
 
   // wave 0 stages the key terms of the next tile: the prefix values are loaded
   // with the tile's DMA and converted after the tile body, so that waiting for
@@ -419,7 +420,12 @@ __device__ __forceinline__ void fwd_bf16_body(
       m_used = max32(u);
     }
     __syncthreads();  // the groups go on by themselves
+  } else if constexpr (SKIP) {
+    wait_all_memory();
+    __syncthreads();  // (the first tile's own wait then finds nothing left)
   }
+  if constexpr (SKIP)
+    skip_norm = __uint_as_float(uniform_u32(__float_as_uint(norm_bound)));
   for (int j = j0; j >= 0; j -= 2 * KS) {
     if (step(j, std::integral_constant<int, 0>())) break;
     if (j >= KS && step(j - KS, std::integral_constant<int, 1>())) break;
