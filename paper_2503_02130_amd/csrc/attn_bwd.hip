@@ -81,7 +81,7 @@ __global__ __launch_bounds__(256) void bwd_delta_kernel(const T* __restrict__ O,
 // double-buffered in LDS through DMA loads, diagonal tile first.  The tile loop
 // is unrolled by two so every LDS address is a per-lane base plus an immediate.
 // Short grids with long rows split the key tiles over two (D = 128) or three (D = 64)
-// groups of four waves (dq_split): B H = 16, L = 3001 97 -> 77 and 70 -> 48 us.
+// groups of four waves (dq_split): B H = 16, L = 3001 88.7 -> 71.0 and 65.2 -> 44.7 us.
 // ---------------------------------------------------------------------------
 constexpr int kBwdThreads = 256;
 constexpr int kDqWaves = 4;

@@ -38,7 +38,7 @@
 //     tile buffers and its own barrier (a count in LDS: with the workgroup's barrier
 //     the groups run in phase and do not fill each other's gaps, at D = 64 10-20 %
 //     slower), and the groups' O, l and m merge in LDS at the end.  B H = 16,
-//     L = 3001: 67.8 -> 55.7 us at D = 128, 46.3 -> 37.0 us at D = 64.
+//     L = 3001: 61.6 -> 51.2 us at D = 128, 42.4 -> 33.7 us at D = 64.
 //   * Causal structure: tiles after a wave's last query are skipped and only the
 //     tile holding its diagonal applies the mask.  Query blocks are dispatched
 //     longest-first with heads fastest, so a head's blocks share an XCD's L2
